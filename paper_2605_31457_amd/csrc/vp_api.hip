@@ -184,6 +184,7 @@ AttendArgs attend_args(const vp_shape* s, const vp_layout* l, const vp_params* p
   a.thr_t = a.thr_s;
   a.tau_s_one = p->tau_score == 1.0f;
   a.nparts = plan.nparts;
+  a.waves = plan.waves;
   a.zs_rows = plan.zs_rows;
   a.zs_gp = plan.zs_gp;
   a.zs = reinterpret_cast<float*>(ws + plan.zs);
@@ -333,7 +334,7 @@ vp_status launch_step(const vp_shape* shape, const vp_layout* layout, const vp_p
   auto ev = [&](int i) -> hipEvent_t { return i < n_events ? static_cast<hipEvent_t>(events[i]) : nullptr; };
   if (hipError_t e = mark(0)) return hip_fail(e, "event record");
   if (use_dual(shape)) {
-    if (hipError_t e = launch_attend(a, MODE_DUAL, dt, hd, st, ev(1), ev(2))) return hip_fail(e, "context pass launch");
+    if (hipError_t e = launch_attend(a, MODE_BOTH, dt, hd, st, ev(1), ev(2))) return hip_fail(e, "context pass launch");
   } else {
     if (hipError_t e = launch_attend(a, MODE_VIS, dt, hd, st)) return hip_fail(e, "visual pass launch");
     if (hipError_t e = launch_attend(a, MODE_TEXT_BOTH, dt, hd, st, ev(1), ev(2))) return hip_fail(e, "text pass launch");
@@ -425,8 +426,8 @@ vp_status vp_visual_mass_timed(const vp_shape* shape, const vp_layout* layout, c
   // events [1] and [2] ride on the text (or one) context launch: its execution alone
   auto ev = [&](int i) -> hipEvent_t { return i < n_events ? static_cast<hipEvent_t>(events[i]) : nullptr; };
   if (hipError_t e = mark(0)) return hip_fail(e, "event record");
-  if (V && use_dual(shape)) {
-    if (hipError_t e = launch_attend(a, MODE_DUAL, shape->dtype, shape->head_dim, st, ev(1), ev(2)))
+  if (use_dual(shape)) {
+    if (hipError_t e = launch_attend(a, V ? MODE_BOTH : MODE_BOTH_STATS, shape->dtype, shape->head_dim, st, ev(1), ev(2)))
       return hip_fail(e, "context pass launch");
   } else {
     if (hipError_t e = launch_attend(a, MODE_VIS, shape->dtype, shape->head_dim, st))

@@ -69,15 +69,10 @@
 #ifndef VP_ATTEND_WAVES_LEAN
 #define VP_ATTEND_WAVES_LEAN 4  // bf16 passes that read only K
 #endif
-#ifndef VP_TILE_SUBS
-#define VP_TILE_SUBS 1  // 32-row sub-tiles whose copies are issued together (context pass)
-#endif
-#ifndef VP_KEPT_SUBS
-#define VP_KEPT_SUBS 1  // same for the kept pass
-#endif
 
 typedef __attribute__((address_space(1))) void global_void;
 typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
 
 // Cache policy of the K/V row copies: non-temporal (the "nt" bit). Every row is
 // used once per step, and streaming it without cache allocation measured ~13%
@@ -93,17 +88,15 @@ constexpr int kRawBufferWord3 = 0x00020000;
 // pass launched alone (64 x 32k batch: visual pass 230 -> 226 us; non-temporal
 // stores: 242), the default in the one-launch context pass (sc1 there: 72B-class
 // decode loop 84.0 -> 84.6 us per step)
-constexpr int spill_policy(int mode) { return (mode & vp::MODE_ONE_LAUNCH) ? 0 : 16; }
+constexpr int spill_policy(int mode) { return vp::base_mode(mode) == vp::MODE_VIS ? 16 : 0; }
 
 namespace vp {
 namespace {
 
 // waves per SIMD the register allocation is sized for (one wave per work-group)
+constexpr bool reads_v(int mode) { return (base_mode(mode) & (MODE_TEXT_ATTN | MODE_KEPT)) != 0; }
 constexpr int attend_waves(int dt, int mode) {
-  return dt != VP_BF16 ? 1
-                       : ((base_mode(mode) == MODE_VIS || base_mode(mode) == MODE_TEXT_STATS)
-                              ? VP_ATTEND_WAVES_LEAN
-                              : VP_ATTEND_WAVES);
+  return dt != VP_BF16 ? 1 : (reads_v(mode) ? VP_ATTEND_WAVES : VP_ATTEND_WAVES_LEAN);
 }
 
 // LDS floor per work-group: 20 KB keeps the bf16 passes that read V at 8
@@ -117,10 +110,23 @@ constexpr int attend_waves(int dt, int mode) {
 #endif
 constexpr int max_i(int x, int y) { return x > y ? x : y; }
 constexpr int lds_floor(int dt, int mode) {
-  return dt != VP_BF16 ? 0
-                       : ((base_mode(mode) == MODE_VIS || base_mode(mode) == MODE_TEXT_STATS)
-                              ? VP_LDS_FLOOR_VIS
-                              : VP_LDS_FLOOR_TEXT);
+  return dt != VP_BF16 ? 0 : (reads_v(mode) ? VP_LDS_FLOOR_TEXT : VP_LDS_FLOOR_VIS);
+}
+
+// Make a value unknown to the optimiser at this point, so that what is computed
+// from it stays where it is instead of being kept in registers through a loop
+// (device code only: the constraints name scalar and vector registers)
+template <typename X>
+__device__ __forceinline__ void unhoist_scalar(X& x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+s"(x));
+#endif
+}
+template <typename X>
+__device__ __forceinline__ void unhoist_vector(X& x) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+v"(x));
+#endif
 }
 
 template <int DT, int D>
@@ -301,10 +307,10 @@ struct Pass {
   static constexpr bool PAGED = (MODE & MODE_PAGED) != 0;        // rows through the block table
   static constexpr bool KEPT = BASE == MODE_KEPT;
   static constexpr bool ZSPILL = KEPT && (MODE & MODE_ZSPILL) != 0;  // kept logits from the spill
-  static constexpr bool VIS = BASE == MODE_VIS;                  // visual rows: statistics + spill
+  static constexpr bool VIS = (BASE & MODE_VIS) != 0;            // visual rows: statistics + spill
   static constexpr bool TSTATS = (BASE & MODE_TEXT_STATS) != 0;  // text rows: statistics
   static constexpr bool ATTN = KEPT || (BASE & MODE_TEXT_ATTN) != 0;
-  static constexpr bool TEXT = !KEPT && !VIS;                    // a text-row pass
+  static constexpr bool TEXT = (BASE & MODE_TEXT_BOTH) != 0;     // text rows: statistics and/or attention
 
   const AttendArgs& a;
   int lane, n16, a4, L, r0, r1, step, h;  // rows [r0, r1) in tiles `step` apart; h: virtual head
@@ -319,13 +325,16 @@ struct Pass {
   int bmask;          // paged caches: rows per block - 1
   float* zbase;  // spill plane of this KV group: row p holds the logits of its heads at position p
                  // (kept pass from the spill: offset to the query's first head)
-  __amdgpu_buffer_rsrc_t zrsrc;  // visual pass: the same plane as a buffer (its full-tile stores)
   QFrag<DT, D> qf;
   // visual pass: lane-local reference and sums (merged over a head's 4 lanes at the end)
   float m_v, Ls_v, Lm_v;
   // text / kept pass: reference shared by a head's 4 lanes, sums and value partial
   float m_t, l_t, Lm_t, Ls_t;
   f32x4 acc[C::ACC_N];
+  // copies after which the swizzle repeats
+  static constexpr int STEPS = C::PIECES / C::RPI < C::COPIES ? max_i(C::PIECES / C::RPI, 1) : C::COPIES;
+  uint32_t row_step[STEPS];  // context passes: init_row_step
+  bool even;
 
   __device__ __forceinline__ explicit Pass(const AttendArgs& a_) : a(a_) {}
 
@@ -343,11 +352,11 @@ struct Pass {
   // does this pass have rows in sub-tile s
   __device__ __forceinline__ bool active(const Sub& s) const {
     if (s.t0 >= r1) return false;
-    if constexpr (VIS) return s.cls != TILE_TEXT;
-    if constexpr (TEXT) return s.cls != TILE_VIS;
+    if constexpr (VIS && !TEXT) return s.cls != TILE_TEXT;
+    if constexpr (TEXT && !VIS) return s.cls != TILE_VIS;
     return true;
   }
-  __device__ __forceinline__ bool needs_v(const Sub& s) const { return ATTN; }
+  __device__ __forceinline__ bool needs_v(const Sub& s) const { return ATTN && (!VIS || s.cls != TILE_VIS); }
 
   __device__ __forceinline__ Sub sub_at(const Sub& prev, int t0, int kp_loaded = -2) const {
     Sub n = prev;
@@ -379,13 +388,14 @@ struct Pass {
 
   // kept pass from the spill: the logits of this lane's 8 rows (head n16 of
   // the query), requested with the tile's V rows; rows past the list read
-  // position 0 and are masked like their V rows
+  // position 0 and are masked like their V rows, lanes without a head read
+  // head 0's (no branch around a load: the compiler would wait for each)
   __device__ __forceinline__ void load_spill(const Sub& s, float (&z)[8]) const {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int p = __shfl(s.kp, 16 * (i >> 2) + 4 * a4 + (i & 3));
       const int pp = (p < 0 || p >= L) ? 0 : p;
-      z[i] = hv ? zbase[static_cast<size_t>(pp) * a.zs_gp + n16] : 0.f;
+      z[i] = zbase[static_cast<size_t>(pp) * a.zs_gp + (hv ? n16 : 0)];
     }
   }
 
@@ -408,15 +418,57 @@ struct Pass {
     }
   }
 
+  // A tile whose 32 rows are all inside the sequence (a context pass) has them
+  // at equal steps from one address, in one physical block when a paged cache's
+  // blocks hold 32 rows or more. Its copies take that address as a buffer and
+  // lane offsets that never change (row_step), so they cost no address
+  // arithmetic; `even` says that the offsets fit 32 bits.
+  __device__ __forceinline__ void init_row_step() {
+    const int rr = lane / C::PIECES;
+    const int slot = lane % C::PIECES;
+#pragma unroll
+    for (int j = 0; j < STEPS; ++j) {
+      const int r = j * C::RPI + rr;
+      row_step[j] = static_cast<uint32_t>(r) * static_cast<uint32_t>(rstride) + 16 * (slot ^ (r & (C::PIECES - 1)));
+    }
+    even = rstride < (1u << 25) && (!PAGED || bmask >= 31);
+  }
+  __device__ __forceinline__ size_t tile_offset(const Sub& s) const {
+    if constexpr (PAGED)
+      return static_cast<size_t>(__builtin_amdgcn_readfirstlane(s.blk)) * bstride +
+             static_cast<size_t>(s.t0 & bmask) * rstride;
+    return static_cast<size_t>(s.t0) * rstride;
+  }
+  __device__ __forceinline__ void copy_even_rows(const char* src, lds_byte* block) const {
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src), 0, 0x7fffffff, kRawBufferWord3);
+#pragma unroll
+    for (int j = 0; j < C::COPIES; ++j)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void*)(block + 1024 * j), 16, row_step[j % STEPS],
+                                               j / STEPS * (STEPS * C::RPI) * static_cast<int>(rstride), 0,
+                                               kCopyPolicy);
+  }
+
   // the 32 rows of a sub-tile from `src` (K or V of this head) into an LDS block
   __device__ __forceinline__ void copy_rows(const char* src, const size_t (&off)[C::COPIES],
-                                            unsigned char* block) const {
+                                            lds_byte* block) const {
 #pragma unroll
     for (int j = 0; j < C::COPIES; ++j)
       __builtin_amdgcn_global_load_lds((global_void*)(src + off[j]), (lds_void*)(block + 1024 * j), 16, 0,
                                        kCopyPolicy);
   }
 
+  // Lane indices that the compiler cannot prove unchanged from tile to tile:
+  // what the rare tiles compute from them is computed there, instead of being
+  // kept in registers through the loop.
+  __device__ __forceinline__ void unhoist_lane() {
+    unhoist_vector(lane);
+    n16 = lane & 15;
+    a4 = lane >> 4;
+  }
+
+  // FULL: 32 rows of one kind, all visible to every query (no masks)
+  template <bool FULL>
   __device__ __forceinline__ void process(const Sub& tile, const unsigned char* kblk, const unsigned char* vblk,
                                          float* stage, const float (&zk)[8]) {
     const int t0 = tile.t0;
@@ -437,6 +489,7 @@ struct Pass {
     }
 
     // value i of this lane is row t0 + 16*(i/4) + 4*a4 + i%4; bit i of the masks
+    // (`valid_rows`: before the causal mask of several queries)
     unsigned valid = 0xffu, vis = 0u;
     if constexpr (KEPT) {
 #pragma unroll
@@ -444,12 +497,15 @@ struct Pass {
         const int p = __shfl(tile.kp, 16 * (i >> 2) + 4 * a4 + (i & 3));  // -1 past the list
         valid &= (p >= 0 && p < L) ? 0xffu : ~(1u << i);
       }
+    } else if constexpr (FULL) {
+      vis = cls == TILE_VIS ? 0xffu : 0u;
     } else {
       if (t_end - t0 < 32) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
           if (t0 + 16 * (i >> 2) + 4 * a4 + (i & 3) >= t_end) valid &= ~(1u << i);
       }
+      const unsigned valid_rows = valid;
       if (t_end > L0) {
         // several queries: the rows after a query's own position are hidden from it
 #pragma unroll
@@ -459,24 +515,24 @@ struct Pass {
       if (cls == TILE_VIS) {
         vis = valid;
       } else if (cls == TILE_MIXED) {
-        SegWalker lw = tile.w;
+        // the segments that meet the tile, one after another (the same for every lane)
+        for (SegWalker lw = tile.w; lw.s < lw.nseg && lw.st < t_end; lw.next()) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int p = t0 + 16 * (i >> 2) + 4 * a4 + (i & 3);
-          if (p < t_end) {
-            lw.seek(p);
-            if (lw.contains(p)) vis |= 1u << i;
+          for (int i = 0; i < 8; ++i) {
+            const int p = t0 + 16 * (i >> 2) + 4 * a4 + (i & 3);
+            if (p >= lw.st && p < lw.en) vis |= 1u << i;
           }
         }
+        vis &= valid_rows;
       }
     }
 
-    if constexpr (VIS) {
+    if (VIS && (!TEXT || cls != TILE_TEXT)) {
       // ---- Eq. (5)/(6) and Eq. (2) statistics over visual rows ----
       float lmax = kNegInf;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
-        if (vis & (1u << i)) lmax = fmaxf(lmax, z[i]);
+        if (FULL || (vis & (1u << i))) lmax = fmaxf(lmax, z[i]);
       const bool up = lmax > m_v + a.thr_s;  // per lane; rare after the first tile
       if (__builtin_amdgcn_ballot_w64(up)) {
         Ls_v *= up ? fast_exp2((m_v - lmax) * a.inv_tau_s) : 1.f;
@@ -486,14 +542,14 @@ struct Pass {
       float ts = 0.f, tm = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float d = (vis & (1u << i)) ? z[i] - m_v : kNegInf;
+        const float d = FULL || (vis & (1u << i)) ? z[i] - m_v : kNegInf;
         ts += fast_exp2(d * a.inv_tau_s);
         tm += fast_exp2(d * a.inv_tau_m);
       }
       Ls_v += ts;
       Lm_v += tm;
       // visual logits: spill rows of zs_gp floats (this KV group's heads) by position
-      if (cls == TILE_VIS && t_end - t0 == 32) {
+      if (FULL || (cls == TILE_VIS && t_end - t0 == 32)) {
         // transpose through the stage (row = token, zs_gp heads): lane (a4, n16)
         // holds head n16 for tokens 16*(i/4) + 4*a4 + i%4; then the 32 rows go
         // out as one contiguous block of 32 * zs_gp floats, 16 bytes per lane
@@ -504,18 +560,20 @@ struct Pass {
         }
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
         const u32x4* src = reinterpret_cast<const u32x4*>(stage);
-        const int soff = t0 * gp * 4;
-        __builtin_amdgcn_raw_buffer_store_b128(src[lane], zrsrc, lane * 16, soff, spill_policy(MODE));
+        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+            zbase + static_cast<size_t>(t0) * gp, 0, 32 * gp * 4, kRawBufferWord3);
+        __builtin_amdgcn_raw_buffer_store_b128(src[lane], rows, lane * 16, 0, spill_policy(MODE));
         if (gp > 8)
-          __builtin_amdgcn_raw_buffer_store_b128(src[64 + lane], zrsrc, 1024 + lane * 16, soff, spill_policy(MODE));
+          __builtin_amdgcn_raw_buffer_store_b128(src[64 + lane], rows, 1024 + lane * 16, 0, spill_policy(MODE));
       } else if (hv && vis) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
           if (vis & (1u << i)) zbase[static_cast<size_t>(t0 + 16 * (i >> 2) + 4 * a4 + (i & 3)) * a.zs_gp + n16] = z[i];
       }
-    } else {
+    }
+    if (KEPT || (TEXT && (!VIS || cls != TILE_VIS))) {
       // ---- text rows (or kept rows): attention weights, statistics, value product ----
-      const unsigned att = valid & ~vis;
+      const unsigned att = FULL ? 0xffu : valid & ~vis;
       float lmax = kNegInf;
 #pragma unroll
       for (int i = 0; i < 8; ++i)
@@ -566,30 +624,155 @@ struct Pass {
 // LDS layout of one pass: per sub-tile a K block, a V block (passes that read
 // V) and a logit stage (visual pass); the total also sets how many work-groups
 // stay resident per CU
-template <int DT, int D, int MODE>
+template <int DT, int D, int MODE, int W>
 struct PassLds {
   using C = Cfg<DT, D>;
   using P = Pass<DT, D, MODE>;
-  static constexpr int NSUB = P::KEPT ? VP_KEPT_SUBS : VP_TILE_SUBS;
   static constexpr int VB = P::ATTN ? C::SUB_ROWS_BYTES : 0;
   static constexpr int SB = P::VIS ? C::STAGE_BYTES : 0;
   static constexpr int SUB = C::SUB_ROWS_BYTES + VB + SB;
-  static constexpr int BYTES = max_i(NSUB * SUB, lds_floor(DT, MODE));
+  static constexpr int BYTES = W > 1 ? SUB : max_i(SUB, lds_floor(DT, MODE));  // per wave
 };
 
-// The work of one work-group (part `part` of KV head g of sequence b; in the
-// kept pass gy = g*T + t also names the query t whose kept list it reads).
-template <int DT, int D, int MODE>
-__device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* lds, int part, int gy, int b) {
+// Per-head statistics of the W waves of a work-group, gathered in LDS
+// ([0..2] visual {m, Ls, Lm}, [3..6] text {m, l, Lm, Ls})
+template <int W>
+struct WaveStats {
+  float v[W][16][8];
+};
+
+// Merges the partials of a work-group's W waves (every wave calls it, waves
+// without tiles included, with m = -inf and sums of zero) and writes the part's
+// statistics and attention partial: maxima and sums meet in LDS (the sums in
+// double), each wave rescales its accumulator to the common maximum and leaves
+// it in its own LDS block (rows padded by four floats: consecutive heads start
+// on different banks), and the block adds the W copies in wave order.
+template <int DT, int D, int MODE, int W>
+__device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, MODE>& s, WaveStats<W>& ws,
+                                              unsigned char* lds, int wave, int part, int g, int b, float m_v,
+                                              float ls_v, float lm_v, float l_t, float lm_t, float ls_t) {
   using C = Cfg<DT, D>;
   using P = Pass<DT, D, MODE>;
-  using Q = PassLds<DT, D, MODE>;
-  constexpr int NSUB = Q::NSUB;
+  constexpr int PITCH = D + 4;
+  static_assert(16 * PITCH * 4 <= PassLds<DT, D, MODE, W>::BYTES, "accumulator rows of a wave");
+  if (s.a4 == 0) {
+    float* o = ws.v[wave][s.n16];
+    if constexpr (P::VIS) {
+      o[0] = m_v;
+      o[1] = ls_v;
+      o[2] = lm_v;
+    }
+    if constexpr (P::TEXT) {
+      o[3] = s.m_t;
+      o[4] = l_t;
+      o[5] = lm_t;
+      o[6] = ls_t;
+    }
+  }
+  __syncthreads();
+  float M = kNegInf;
+  if constexpr (P::TEXT) {
+#pragma unroll
+    for (int w = 0; w < W; ++w) M = fmaxf(M, ws.v[w][s.n16][3]);
+  }
+  if constexpr (P::ATTN) {
+    const float f = s.m_t == kNegInf ? 0.f : fast_exp2(s.m_t - M);
+#pragma unroll
+    for (int i = 0; i < C::ACC_N; ++i) s.acc[i] *= f;
+    store_acc<DT, D, C::ACC_N>(reinterpret_cast<float*>(lds + wave * PassLds<DT, D, MODE, W>::BYTES) + s.n16 * PITCH,
+                               s.acc, s.a4);
+  }
+  const size_t head0 = static_cast<size_t>(b) * a.T * a.Hq + static_cast<size_t>(g) * a.T * a.G;
+  if (wave == 0 && s.a4 == 0 && s.hv) {
+    float* st = a.stats + ((head0 + s.n16) * a.nparts + part) * 8;
+    if constexpr (P::VIS) {
+      float Mv = kNegInf;
+#pragma unroll
+      for (int w = 0; w < W; ++w) Mv = fmaxf(Mv, ws.v[w][s.n16][0]);
+      double ls = 0.0, lm = 0.0;
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        const float* o = ws.v[w][s.n16];
+        if (o[0] != kNegInf) {
+          ls += static_cast<double>(fast_exp2((o[0] - Mv) * a.inv_tau_s)) * o[1];
+          lm += static_cast<double>(fast_exp2((o[0] - Mv) * a.inv_tau_m)) * o[2];
+        }
+      }
+      *reinterpret_cast<float4*>(st) = make_float4(Mv, static_cast<float>(ls), static_cast<float>(lm), 0.f);
+    }
+    if constexpr (P::TEXT) {
+      double l = 0.0, lm = 0.0, ls = 0.0;
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        const float* o = ws.v[w][s.n16];
+        if (o[3] != kNegInf) {
+          l += static_cast<double>(fast_exp2(o[3] - M)) * o[4];
+          if constexpr (P::TSTATS) {
+            lm += static_cast<double>(fast_exp2((o[3] - M) * a.inv_tau_m)) * o[5];
+            ls += static_cast<double>(fast_exp2((o[3] - M) * a.inv_tau_s)) * o[6];
+          }
+        }
+      }
+      if constexpr (P::TSTATS)
+        *reinterpret_cast<float4*>(st + 4) =
+            make_float4(M, static_cast<float>(l), static_cast<float>(lm), static_cast<float>(ls));
+      else
+        *reinterpret_cast<float2*>(st + 4) = make_float2(M, static_cast<float>(l));
+    }
+  }
+  if constexpr (P::ATTN) {
+    __syncthreads();
+    constexpr int COLS = D / 4;
+    for (int i = threadIdx.x; i < a.T * a.G * COLS; i += 64 * W) {
+      const int h = i / COLS, c = i % COLS;
+      float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        const float4 x = reinterpret_cast<const float4*>(
+            reinterpret_cast<const float*>(lds + w * PassLds<DT, D, MODE, W>::BYTES) + h * PITCH)[c];
+        t.x += x.x;
+        t.y += x.y;
+        t.z += x.z;
+        t.w += x.w;
+      }
+      reinterpret_cast<float4*>(a.acc + ((head0 + h) * a.nparts + part) * D)[c] = t;
+    }
+  }
+}
+
+// Once per sequence in a launch with the visual role, by one wave: a new step's
+// arrival counters of the sequence's T*U selection rows at zero, and the
+// sequence's clipped segment table (positions and visual ranks) for the select
+// kernel. A wave of the sequence's last part of KV head 0 does it after its
+// tiles (the launch of one-wave work-groups has a work-group more for it).
+__device__ __forceinline__ void step_setup(const AttendArgs& a, int b) {
+  const int lane = threadIdx.x & 63;
+  if (a.sync)
+    for (int i = lane; i < a.T * a.U; i += 64) a.sync[static_cast<size_t>(b) * a.T * a.U + i] = 0u;
+  if (a.segtab) {
+    const int L = vis_len(clamp_len(a.seq_len[b], a.max_seq_len), a.T);
+    const int o0 = a.seg_off[b];
+    load_segments(static_cast<SegTable*>(a.segtab)[b], a.seg + 2 * static_cast<long>(o0), a.seg_off[b + 1] - o0, L,
+                  lane);
+  }
+}
+
+// The work of one wave (part `part` of KV head g of sequence b; in the kept
+// pass gy = g*T + t also names the query t whose kept list it reads). Of the W
+// waves that share a part, wave w takes the tiles part + nparts*w, every
+// nparts*W; the kept pass has one wave per part.
+template <int DT, int D, int MODE, int W = 1>
+__device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* lds_block, int part, int gy, int b,
+                                            int wave = 0, WaveStats<W>* ws = nullptr) {
+  using C = Cfg<DT, D>;
+  using P = Pass<DT, D, MODE>;
+  using Q = PassLds<DT, D, MODE, W>;
   constexpr int VB = Q::VB;
-  constexpr int SUB = Q::SUB;
+  unsigned char* lds = lds_block + wave * Q::BYTES;
+  lds_byte* lds_dma = (lds_byte*)lds;  // the copies' view of it (converted once: a generic pointer may be null)
 
   P s(a);
-  s.lane = threadIdx.x;
+  s.lane = threadIdx.x & 63;
   s.n16 = s.lane & 15;
   s.a4 = s.lane >> 4;
   s.L = clamp_len(a.seq_len[b], a.max_seq_len);
@@ -614,14 +797,14 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
     s.r1 = s.L == 0 ? s.r0 : min(s.r0 + a.split, kb);
     s.step = 32;
   } else {
-    s.r0 = 32 * part;
+    s.r0 = 32 * (part + a.nparts * wave);
     s.r1 = s.L;
-    s.step = 32 * a.nparts;
+    s.step = 32 * a.nparts * W;
   }
   // the query rows load while the length and the budget arrive
   const size_t qrow = s.hv ? (static_cast<size_t>(b) * a.T + tq) * a.Hq + g * a.G + (vh - tq * a.G) : 0;
   load_q<DT, D>(s.qf, static_cast<const char*>(a.q) + qrow * C::ROWB, s.hv, s.a4);
-  if (s.r0 >= s.r1) {
+  if (W == 1 && s.r0 >= s.r1) {
     // no rows: an empty partial (max -inf, sum 0), so that the merge can read
     // every part's slot without first learning the length and the budget
     if constexpr (P::ATTN) {
@@ -653,19 +836,13 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
   s.bt = paged ? a.block_table + static_cast<size_t>(b) * a.nblk : nullptr;
   s.bstride = static_cast<size_t>(a.sb) * C::ESZ;
   s.bmask = paged ? (1 << a.bs_log2) - 1 : 0;
+  if constexpr (!P::KEPT) s.init_row_step();
   s.m_v = kNegInf;
   s.Ls_v = s.Lm_v = 0.f;
   s.m_t = kNegInf;
   s.l_t = s.Lm_t = s.Ls_t = 0.f;
 #pragma unroll
   for (int i = 0; i < C::ACC_N; ++i) s.acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if constexpr (P::VIS) {
-    // the plane (zs_rows * zs_gp floats) as a raw buffer: offsets past it are dropped
-    const size_t plane = static_cast<size_t>(a.zs_rows) * a.zs_gp * 4;
-    s.zrsrc = __builtin_amdgcn_make_buffer_rsrc(
-        a.zs + (static_cast<size_t>(b) * a.Hkv + g) * a.zs_rows * static_cast<size_t>(a.zs_gp), 0,
-        static_cast<int>(plane < 0x7fffffffu ? plane : 0x7fffffffu), kRawBufferWord3);
-  }
   s.zbase = (P::VIS || P::ZSPILL)
                 ? a.zs + (static_cast<size_t>(b) * a.Hkv + g) * a.zs_rows * static_cast<size_t>(a.zs_gp) + qk * a.G
                 : nullptr;
@@ -679,57 +856,101 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
   }
   cur = s.sub_at(cur, s.r0, kp0);
 
-  // tiles of NSUB sub-tiles: all copies of a tile are issued before any of it is used
+  // All copies of a step are issued before any of it is used. A step is one tile,
+  // or, with both roles, two visual tiles of the wave (the second one's K rows in
+  // the block that holds a text tile's V rows), so that a wave has 16 KB in
+  // flight whatever its tiles hold.
+  constexpr bool PAIRS = P::VIS && P::ATTN;
   while (cur.t0 < s.r1) {
-    Sub sub[NSUB];
-    bool act[NSUB];
-    sub[0] = cur;
-#pragma unroll
-    for (int i = 1; i < NSUB; ++i) sub[i] = s.sub_at(sub[i - 1], sub[i - 1].t0 + s.step);
-#pragma unroll
-    for (int i = 0; i < NSUB; ++i) act[i] = s.active(sub[i]);
-    // The work-group is a single wave, so ordering needs counters, not barriers
-    // (a barrier's release fence would also wait for the logit stores of the
-    // previous tile). LDS reads of the previous tile must have returned before
-    // the copies overwrite it:
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    float zk[NSUB][8];
-#pragma unroll
-    for (int i = 0; i < NSUB; ++i) {
-      if (act[i]) {
-        unsigned char* blk = lds + i * SUB;
-        size_t off[C::COPIES];
-        s.row_offsets(sub[i], off);
-        if constexpr (!P::ZSPILL) s.copy_rows(s.Kb, off, blk);
-        if (s.needs_v(sub[i])) s.copy_rows(s.Vb, off, blk + C::SUB_ROWS_BYTES);
-        if constexpr (P::ZSPILL) s.load_spill(sub[i], zk[i]);
+    const Sub t0 = cur;
+    const bool act = s.active(t0);
+    Sub t1 = t0;
+    bool pair = false;
+    if constexpr (PAIRS) {
+      if (t0.cls == TILE_VIS) {
+        t1 = s.sub_at(t0, t0.t0 + s.step);
+        pair = t1.t0 < s.r1 && t1.cls == TILE_VIS;
       }
     }
-    // the next tile's kept positions / segment state load while these copies fly
-    cur = s.sub_at(sub[NSUB - 1], sub[NSUB - 1].t0 + s.step);
+    // The work-group's waves share nothing here, so ordering needs counters, not
+    // barriers (a barrier's release fence would also wait for the logit stores of
+    // the previous tile). LDS reads of the previous tile must have returned before
+    // the copies overwrite it:
+    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+    float zk[8];
+    if (act) {
+      // the 16 copy destinations are added up per tile, not held in scalar registers
+      lds_byte* dma = lds_dma;
+      if constexpr (W > 1) unhoist_scalar(dma);
+      if (!P::KEPT && s.even && t0.t0 + 32 <= s.L) {
+        const size_t off = s.tile_offset(t0);
+        s.copy_even_rows(s.Kb + off, dma);
+        if (s.needs_v(t0)) s.copy_even_rows(s.Vb + off, dma + C::SUB_ROWS_BYTES);
+      } else {
+        size_t off[C::COPIES];
+        if constexpr (!P::KEPT) s.unhoist_lane();
+        s.row_offsets(t0, off);
+        if constexpr (!P::ZSPILL) s.copy_rows(s.Kb, off, dma);
+        if (s.needs_v(t0)) s.copy_rows(s.Vb, off, dma + C::SUB_ROWS_BYTES);
+      }
+      if (pair) {
+        if (s.even && t1.t0 + 32 <= s.L) {
+          s.copy_even_rows(s.Kb + s.tile_offset(t1), dma + C::SUB_ROWS_BYTES);
+        } else {
+          size_t off[C::COPIES];
+          s.unhoist_lane();
+          s.row_offsets(t1, off);
+          s.copy_rows(s.Kb, off, dma + C::SUB_ROWS_BYTES);
+        }
+      }
+      if constexpr (P::ZSPILL) s.load_spill(t0, zk);
+    }
+    // the next step's kept positions / segment state load while these copies fly
+    cur = s.sub_at(pair ? t1 : t0, (pair ? t1.t0 : t0.t0) + s.step);
     // the copies have landed in LDS once the vector-memory counter drains
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
-#pragma unroll
-    for (int i = 0; i < NSUB; ++i)
-      if (act[i])
-        s.process(sub[i], lds + i * SUB, lds + i * SUB + C::SUB_ROWS_BYTES,
-                  reinterpret_cast<float*>(lds + i * SUB + C::SUB_ROWS_BYTES + VB), zk[i]);
+    if (!act) continue;
+    unsigned char* kblk = lds;
+    unsigned char* vblk = lds + C::SUB_ROWS_BYTES;
+    float* stage = reinterpret_cast<float*>(vblk + VB);
+    Sub t = t0;
+#pragma unroll 1
+    for (int i = 0;; ++i) {
+      if (!P::KEPT && t.cls != TILE_MIXED && t.t0 + 32 <= min(s.L, s.L0)) {
+        s.template process<true>(t, kblk, vblk, stage, zk);
+      } else {
+        if constexpr (!P::KEPT) s.unhoist_lane();
+        s.template process<false>(t, kblk, vblk, stage, zk);
+      }
+      if (!PAIRS || !pair || i == 1) break;
+      t = t1;
+      kblk = vblk;
+    }
   }
 
   // ---- write this part's partials ----
+  float M_v = kNegInf, ls_v = 0.f, lm_v = 0.f;
   if constexpr (P::VIS) {
     // merge the four lanes' statistics onto their common maximum
-    const float M = max_over_quads(s.m_v);
+    M_v = max_over_quads(s.m_v);
     const bool any = s.m_v != kNegInf;
-    const float fs = any ? fast_exp2((s.m_v - M) * a.inv_tau_s) : 0.f;
-    const float fm = any ? fast_exp2((s.m_v - M) * a.inv_tau_m) : 0.f;
-    const float s_ls = sum_over_quads(s.Ls_v * fs);
-    const float s_lm = sum_over_quads(s.Lm_v * fm);
-    if (s.hv && s.a4 == 0) {
+    const float fs = any ? fast_exp2((s.m_v - M_v) * a.inv_tau_s) : 0.f;
+    const float fm = any ? fast_exp2((s.m_v - M_v) * a.inv_tau_m) : 0.f;
+    ls_v = sum_over_quads(s.Ls_v * fs);
+    lm_v = sum_over_quads(s.Lm_v * fm);
+    if (W == 1 && s.hv && s.a4 == 0) {
       float* st = a.stats + ((static_cast<size_t>(b) * a.T * a.Hq + s.h) * a.nparts + part) * 8;
-      *reinterpret_cast<float4*>(st) = make_float4(M, s_ls, s_lm, 0.f);
+      *reinterpret_cast<float4*>(st) = make_float4(M_v, ls_v, lm_v, 0.f);
     }
-  } else {
+  }
+  if constexpr (W > 1) {
+    if (P::VIS && g == 0 && part == a.nparts - 1 && wave == W - 1) step_setup(a, b);
+    const float s_lt = P::TEXT ? sum_over_quads(s.l_t) : 0.f;
+    const float s_lm = P::TSTATS ? sum_over_quads(s.Lm_t) : 0.f;
+    const float s_ls = P::TSTATS ? (a.tau_s_one ? s_lt : sum_over_quads(s.Ls_t)) : 0.f;
+    combine_waves<DT, D, MODE, W>(a, s, *ws, lds_block, wave, part, g, b, M_v, ls_v, lm_v, s_lt, s_lm, s_ls);
+  } else if constexpr (P::KEPT || P::TEXT) {
+    static_assert(!(P::VIS && P::TEXT), "both roles: several waves per work-group");
     const float s_lt = sum_over_quads(s.l_t);
     const float s_lm = P::TSTATS ? sum_over_quads(s.Lm_t) : 0.f;
     const float s_ls = P::TSTATS ? (a.tau_s_one ? s_lt : sum_over_quads(s.Ls_t)) : 0.f;
@@ -752,112 +973,116 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
   }
 }
 
-// The extra work-group of a launch with the visual role (x = its last index,
-// KV head 0): a new step's arrival counters of the sequence's T*U selection
-// rows at zero, and the sequence's clipped segment table (positions and visual
-// ranks) for the select kernel.
-__device__ __forceinline__ void step_setup(const AttendArgs& a, int g, int b) {
-  if (g != 0) return;
-  const int lane = threadIdx.x;
-  if (a.sync)
-    for (int i = lane; i < a.T * a.U; i += 64) a.sync[static_cast<size_t>(b) * a.T * a.U + i] = 0u;
-  if (a.segtab) {
-    const int L = vis_len(clamp_len(a.seq_len[b], a.max_seq_len), a.T);
-    const int o0 = a.seg_off[b];
-    load_segments(static_cast<SegTable*>(a.segtab)[b], a.seg + 2 * static_cast<long>(o0), a.seg_off[b + 1] - o0, L,
-                  lane);
-  }
-}
-
 template <int DT, int D, int MODE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(attend_waves(DT, MODE)))) void attend_kernel(
     const AttendArgs a) {
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[PassLds<DT, D, MODE>::BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[PassLds<DT, D, MODE, 1>::BYTES];
   if (base_mode(MODE) == MODE_VIS && static_cast<int>(blockIdx.x) == a.nparts) {
-    step_setup(a, blockIdx.y, blockIdx.z);
+    if (blockIdx.y == 0) step_setup(a, blockIdx.z);
     return;
   }
   attend_body<DT, D, MODE>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
-// Both context passes in one launch (grid.x = 2 parts + 1): work-group 2p takes
-// the text role of part p, 2p + 1 its visual role, the last one the step setup.
-// Used up to mid-size caches, where launch latency and load balance, not the
-// visual spill's interference with the text stream, bound the step.
-template <int DT, int D, int PG>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(attend_waves(DT, MODE_TEXT_BOTH)))) void
-attend_dual_kernel(const AttendArgs a) {
-  constexpr int VIS = MODE_VIS | MODE_ONE_LAUNCH | PG;
-  constexpr int TEXT = MODE_TEXT_BOTH | MODE_ONE_LAUNCH | PG;
-  constexpr int BYTES = max_i(PassLds<DT, D, VIS>::BYTES, PassLds<DT, D, TEXT>::BYTES);
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[BYTES];
-  const int x = blockIdx.x;
-  // the roles alternate, so every CU gets a mix of visual (K, spill) and text
-  // (K and V) work-groups (measured 86.5 -> 84.8 us at the 16-sequence ragged batch)
-  if (x < 2 * a.nparts) {
-    if (x & 1) attend_body<DT, D, VIS>(a, lds, x >> 1, blockIdx.y, blockIdx.z);
-    else attend_body<DT, D, TEXT>(a, lds, x >> 1, blockIdx.y, blockIdx.z);
-  } else {
-    step_setup(a, blockIdx.y, blockIdx.z);
-  }
+// The index of this thread's wave in its work-group, as a scalar
+__device__ __forceinline__ int wave_index() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6); }
+
+// W waves per part: both roles of the context pass in one launch (MODE_BOTH,
+// or MODE_BOTH_STATS when no V is given). Every
+// wave takes whatever its tiles hold: a visual tile's K rows, a text tile's K
+// and V rows (a mixed tile is read once for both).
+template <int DT, int D, int MODE, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(attend_waves(DT, MODE)))) void
+attend_waves_kernel(const AttendArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[W * PassLds<DT, D, MODE, W>::BYTES];
+  __shared__ WaveStats<W> ws;
+  const int wave = wave_index();
+  attend_body<DT, D, MODE, W>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z, wave, &ws);
 }
 
 // A later layer's text attention pass and kept pass in one launch (their rows
 // are disjoint and the kept list is the anchor layer's, known before the
-// launch): grid.x = P text parts + T*splits kept work-groups per (KV head,
-// sequence); each work-group does what it does in its own launch, so the
-// partials are the same bits, and the kept work-groups fill the text pass's tail.
-template <int DT, int D, int PG>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(attend_waves(DT, MODE_TEXT_ATTN)))) void
+// launch): per (KV head, sequence) the work-groups of the text parts, then those
+// of T*splits kept splits, one split per wave. Each does what it does in its
+// own launch, so the partials are the same bits, and the kept work-groups fill
+// the text pass's tail.
+template <int DT, int D, int PG, int W>
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(attend_waves(DT, MODE_TEXT_ATTN)))) void
 attend_text_kept_kernel(const AttendArgs a) {
   constexpr int TEXT = MODE_TEXT_ATTN | PG;
   constexpr int KEPT = MODE_KEPT | PG;
-  constexpr int BYTES = max_i(PassLds<DT, D, TEXT>::BYTES, PassLds<DT, D, KEPT>::BYTES);
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[BYTES];
+  static_assert(PassLds<DT, D, TEXT, W>::BYTES == PassLds<DT, D, KEPT, W>::BYTES, "LDS blocks of the waves");
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[W * PassLds<DT, D, TEXT, W>::BYTES];
+  __shared__ WaveStats<W> ws;
   const int x = blockIdx.x;
+  const int wave = wave_index();
   if (x < a.nparts) {
-    attend_body<DT, D, TEXT>(a, lds, x, blockIdx.y, blockIdx.z);
+    attend_body<DT, D, TEXT, W>(a, lds, x, blockIdx.y, blockIdx.z, wave, &ws);
   } else {
-    const int j = x - a.nparts;
+    const int j = (x - a.nparts) * W + wave;
     const int t = j / a.nsplit;
-    attend_body<DT, D, KEPT>(a, lds, j - t * a.nsplit, blockIdx.y * a.T + t, blockIdx.z);
+    if (t < a.T)
+      attend_body<DT, D, KEPT>(a, lds + wave * PassLds<DT, D, KEPT, W>::BYTES, j - t * a.nsplit, blockIdx.y * a.T + t,
+                               blockIdx.z);
   }
 }
 
 // Launches one pass. With events given, they are attached to the launch itself
 // (hipExtLaunchKernel): they time the kernel's execution alone, as a profiler does.
 template <typename K>
-hipError_t launch_one(K kernel, dim3 grid, const AttendArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+hipError_t launch_one(K kernel, dim3 grid, int threads, const AttendArgs& a, hipStream_t st, hipEvent_t ev0,
+                      hipEvent_t ev1) {
   if (ev0 || ev1) {
     void* args[1] = {const_cast<AttendArgs*>(&a)};
-    return hipExtLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3(64), args, 0, st, ev0, ev1, 0);
+    return hipExtLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3(threads), args, 0, st, ev0, ev1, 0);
   }
-  hipLaunchKernelGGL(kernel, grid, dim3(64), 0, st, a);
+  hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, a);
   return hipGetLastError();
+}
+
+// the one-wave passes of large caches, and the kept pass
+template <int DT, int D, int PG>
+hipError_t launch_single(const AttendArgs& a, int mode, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  const bool kept = base_mode(mode) == MODE_KEPT;
+  int gx = a.nparts;
+  if (kept) gx = a.nsplit;
+  else if (mode == MODE_VIS) gx = a.nparts + 1;  // the step setup
+  else if (mode == MODE_TEXT_KEPT) gx = a.nparts + a.T * a.nsplit;
+  const dim3 grid(gx, kept ? a.Hkv * a.T : a.Hkv, a.B);
+  switch (mode) {
+    case MODE_TEXT_KEPT: return launch_one(attend_text_kept_kernel<DT, D, PG, 1>, grid, 64, a, st, ev0, ev1);
+    case MODE_VIS: return launch_one(attend_kernel<DT, D, MODE_VIS | PG>, grid, 64, a, st, ev0, ev1);
+    case MODE_TEXT_STATS: return launch_one(attend_kernel<DT, D, MODE_TEXT_STATS | PG>, grid, 64, a, st, ev0, ev1);
+    case MODE_TEXT_ATTN: return launch_one(attend_kernel<DT, D, MODE_TEXT_ATTN | PG>, grid, 64, a, st, ev0, ev1);
+    case MODE_TEXT_BOTH: return launch_one(attend_kernel<DT, D, MODE_TEXT_BOTH | PG>, grid, 64, a, st, ev0, ev1);
+    case MODE_KEPT: return launch_one(attend_kernel<DT, D, MODE_KEPT | PG>, grid, 64, a, st, ev0, ev1);
+    case MODE_KEPT | MODE_ZSPILL:
+      return launch_one(attend_kernel<DT, D, MODE_KEPT | MODE_ZSPILL | PG>, grid, 64, a, st, ev0, ev1);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// the passes with kPartWaves waves per part
+template <int DT, int D, int PG>
+hipError_t launch_waves(const AttendArgs& a, int mode, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  constexpr int W = kPartWaves;
+  int gx = a.nparts;
+  if (mode == MODE_TEXT_KEPT) gx = a.nparts + (a.T * a.nsplit + W - 1) / W;
+  const dim3 grid(gx, a.Hkv, a.B);
+  switch (mode) {
+    case MODE_TEXT_ATTN:  // the text parts alone
+    case MODE_TEXT_KEPT: return launch_one(attend_text_kept_kernel<DT, D, PG, W>, grid, 64 * W, a, st, ev0, ev1);
+    case MODE_BOTH: return launch_one(attend_waves_kernel<DT, D, MODE_BOTH | PG, W>, grid, 64 * W, a, st, ev0, ev1);
+    case MODE_BOTH_STATS:
+      return launch_one(attend_waves_kernel<DT, D, MODE_BOTH_STATS | PG, W>, grid, 64 * W, a, st, ev0, ev1);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 template <int DT, int D, int PG>
 hipError_t launch_dd(const AttendArgs& a, int mode, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-  // launches with the visual role carry one more work-group per sequence (step_setup)
-  const bool kept = (mode & ~MODE_ZSPILL) == MODE_KEPT;
-  int gx = a.nparts;
-  if (kept) gx = a.nsplit;
-  else if (mode == MODE_DUAL) gx = 2 * a.nparts + 1;
-  else if (mode == MODE_VIS) gx = a.nparts + 1;
-  else if (mode == MODE_TEXT_KEPT) gx = a.nparts + a.T * a.nsplit;  // text parts, then kept splits
-  const dim3 grid(gx, kept ? a.Hkv * a.T : a.Hkv, a.B);
-  switch (mode) {
-    case MODE_TEXT_KEPT: return launch_one(attend_text_kept_kernel<DT, D, PG>, grid, a, st, ev0, ev1);
-    case MODE_DUAL: return launch_one(attend_dual_kernel<DT, D, PG>, grid, a, st, ev0, ev1);
-    case MODE_VIS: return launch_one(attend_kernel<DT, D, MODE_VIS | PG>, grid, a, st, ev0, ev1);
-    case MODE_TEXT_STATS: return launch_one(attend_kernel<DT, D, MODE_TEXT_STATS | PG>, grid, a, st, ev0, ev1);
-    case MODE_TEXT_ATTN: return launch_one(attend_kernel<DT, D, MODE_TEXT_ATTN | PG>, grid, a, st, ev0, ev1);
-    case MODE_TEXT_BOTH: return launch_one(attend_kernel<DT, D, MODE_TEXT_BOTH | PG>, grid, a, st, ev0, ev1);
-    case MODE_KEPT: return launch_one(attend_kernel<DT, D, MODE_KEPT | PG>, grid, a, st, ev0, ev1);
-    case MODE_KEPT | MODE_ZSPILL:
-      return launch_one(attend_kernel<DT, D, MODE_KEPT | MODE_ZSPILL | PG>, grid, a, st, ev0, ev1);
-    default: return hipErrorInvalidValue;
-  }
+  return a.waves == 1 || base_mode(mode) == MODE_KEPT ? launch_single<DT, D, PG>(a, mode, st, ev0, ev1)
+                                                      : launch_waves<DT, D, PG>(a, mode, st, ev0, ev1);
 }
 
 }  // namespace

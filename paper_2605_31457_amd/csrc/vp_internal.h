@@ -23,10 +23,17 @@ __host__ __device__ inline int vhead(int h, int t, int G, int T) { return (h / G
 // last T - 1 positions are the other queries' tokens (text)
 __host__ __device__ inline int vis_len(int L, int T) { return L - T + 1 > 0 ? L - T + 1 : 0; }
 
+// Waves that share a context-pass part when both roles run in one launch
+#ifndef VP_PART_WAVES
+#define VP_PART_WAVES 4
+#endif
+constexpr int kPartWaves = VP_PART_WAVES;
+
 // Work decomposition and workspace carving, a pure function of the shape.
 struct Plan {
   int nparts;   // context-pass work-groups per (sequence, KV head); part p takes
                 // the 32-row tiles p, p + nparts, p + 2 nparts, ...
+  int waves;    // waves per context-pass work-group (kPartWaves, or 1 with the passes in two launches)
   int split;    // kept rows per kept-pass work-group (multiple of 32)
   int nsplit;   // ceil(k_cap / split)
   bool text_kept_one_launch;  // a later layer's text and kept passes fit one resident round together
@@ -64,14 +71,14 @@ enum Mode : int {
   MODE_TEXT_ATTN = 4,   // text rows: attention partial (reads V)
   MODE_TEXT_BOTH = 6,
   MODE_KEPT = 8,        // kept visual rows: attention partial
-  MODE_DUAL = 16,       // visual pass and text pass (statistics + attention) in one launch
+  MODE_BOTH_STATS = 3,  // visual and text rows in one launch, no V given
+  MODE_BOTH = 7,        // visual and text rows in one launch (statistics + attention)
   MODE_PAGED = 32,      // flag: K and V rows addressed through a block table (paged caches)
   MODE_ZSPILL = 64,     // flag (kept pass): the kept rows' logits come from the visual pass's
                         // spill of the same step instead of their K rows (V rows only are read)
-  MODE_ONE_LAUNCH = 128, // flag: a role of the one-launch context pass (attend_dual_kernel)
   MODE_TEXT_KEPT = 256   // launch of a later layer: the text attention pass and the kept pass together
 };
-constexpr int base_mode(int mode) { return mode & ~(MODE_PAGED | MODE_ZSPILL | MODE_ONE_LAUNCH); }
+constexpr int base_mode(int mode) { return mode & ~(MODE_PAGED | MODE_ZSPILL); }
 
 struct AttendArgs {
   const void* q;
@@ -94,6 +101,7 @@ struct AttendArgs {
   float thr_t;          // same for the attention partial
   int tau_s_one;        // tau_score == 1: the attention weight doubles as the score weight
   int nparts;
+  int waves;            // waves per context-pass work-group
   int zs_rows, zs_gp;
   float* zs;
   float* stats;

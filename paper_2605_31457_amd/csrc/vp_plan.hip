@@ -14,12 +14,13 @@ int queries(const vp_shape& s) { return s.n_queries > 1 ? s.n_queries : 1; }
 int rows_per_query(const vp_shape& s) { return s.scope == VP_SCOPE_KV_GROUP ? s.n_kv_heads : 1; }
 int rows_per_seq(const vp_shape& s) { return queries(s) * rows_per_query(s); }
 
-// Context-pass work-groups of the one launch of both passes: 2048 (1024 parts
-// per role) is one resident round (8 work-groups per CU x 256 CUs), so no
-// work-group waits for a second round; measured best against 768 to 1280
-// parts per role at the ragged 16-sequence batch and the 72B-class loop.
-#ifndef VP_TARGET_PARTS
-#define VP_TARGET_PARTS 2048
+// Waves of the one launch of both passes: one resident round (8 waves per CU x
+// 256 CUs), so no work-group waits for a second round.
+#ifndef VP_ONE_LAUNCH_WAVES
+#define VP_ONE_LAUNCH_WAVES 2048
+#endif
+#ifndef VP_ONE_LAUNCH_TILES
+#define VP_ONE_LAUNCH_TILES 1  // 32-row tiles per wave of the one launch, at least
 #endif
 // The visual and text passes in two launches (large caches) take three
 // quarters of that: 6 parts per KV head at the 64 x 32k batch, where 4, 5, 6,
@@ -40,9 +41,6 @@ int rows_per_seq(const vp_shape& s) { return queries(s) * rows_per_query(s); }
 // one launch with half the parts; the 64 x 32k batch (262k tiles) loses 100 us.
 #ifndef VP_DUAL_MAX_TILES
 #define VP_DUAL_MAX_TILES 32768  // 32-row tiles over the batch and KV heads
-#endif
-#ifndef VP_DUAL_PART_DIV
-#define VP_DUAL_PART_DIV 2  // parts of the one-launch context pass: VP_TARGET_PARTS / this
 #endif
 bool use_dual(const vp_shape* s) {
   const int64_t tiles = static_cast<int64_t>(s->batch) * s->n_kv_heads * ((s->max_seq_len + 31) / 32);
@@ -71,9 +69,11 @@ Plan make_plan(const vp_shape& s) {
   const int64_t pairs = static_cast<int64_t>(s.batch) * s.n_kv_heads;
   const int64_t tiles = (s.max_seq_len + 31) / 32;
   // the one-launch context pass runs a visual and a text work-group per part
-  const int64_t target = use_dual(&s) ? VP_TARGET_PARTS / VP_DUAL_PART_DIV : VP_TWO_LAUNCH_PARTS;
-  int64_t parts = (target + pairs - 1) / pairs;
-  if (parts > (tiles + VP_MIN_TILES - 1) / VP_MIN_TILES) parts = (tiles + VP_MIN_TILES - 1) / VP_MIN_TILES;
+  const bool one_launch = use_dual(&s);
+  p.waves = one_launch ? kPartWaves : 1;
+  const int64_t min_tiles = one_launch ? kPartWaves * VP_ONE_LAUNCH_TILES : VP_MIN_TILES;
+  int64_t parts = one_launch ? VP_ONE_LAUNCH_WAVES / (kPartWaves * pairs) : (VP_TWO_LAUNCH_PARTS + pairs - 1) / pairs;
+  if (parts > (tiles + min_tiles - 1) / min_tiles) parts = (tiles + min_tiles - 1) / min_tiles;
   if (parts < 1) parts = 1;
   p.nparts = static_cast<int>(parts);
   // Kept pass: the fewest kept rows per work-group (32, 64, 128, ...) that
@@ -96,8 +96,9 @@ Plan make_plan(const vp_shape& s) {
   // work-groups then fill the text pass's tail (8 layers: 131.8 -> 98.6 us at the
   // 1-sequence batch, 381.9 -> 351.9 at the 72B-class loop); beyond one round
   // the text pass is split over two (the 64 x 32k batch: 3081 -> 3663 us).
-  p.text_kept_one_launch = static_cast<int64_t>(p.nparts + queries(s) * p.nsplit) * s.n_kv_heads * s.batch <=
-                           static_cast<int64_t>(VP_KEPT_WGS);
+  p.text_kept_one_launch =
+      one_launch ? pairs * queries(s) * p.nsplit <= VP_KEPT_WGS / 2
+                 : (p.nparts + static_cast<int64_t>(queries(s)) * p.nsplit) * pairs <= VP_KEPT_WGS;
   // A step whose kept pass would be a handful of work-groups folds the kept
   // rows into the merge (their K and V rows read there): bf16 caches, every
   // text part and kept row in one batch per head.
