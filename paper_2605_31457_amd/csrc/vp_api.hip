@@ -195,7 +195,6 @@ AttendArgs attend_args(const vp_shape* s, const vp_layout* l, const vp_params* p
   a.nsplit = plan.nsplit;
   a.kstats = reinterpret_cast<float*>(ws + plan.kstats);
   a.kacc = reinterpret_cast<float*>(ws + plan.kacc);
-  a.sync = reinterpret_cast<uint32_t*>(ws + plan.sync);
   a.segtab = ws + plan.segtab;
   return a;
 }
@@ -349,7 +348,9 @@ vp_status launch_step(const vp_shape* shape, const vp_layout* layout, const vp_p
   t.vis_idx = vis_idx;
   t.chunk = plan.sel_chunk;
   t.nchunks = plan.sel_chunks;
-  t.sync = a.sync;
+  t.kacc = a.kacc;
+  t.nsplit = plan.nsplit;
+  t.head_dim = hd;
   t.segtab = a.segtab;
   if (hipError_t e = launch_select(t, st)) return hip_fail(e, "select launch");
   if (hipError_t e = mark(3)) return hip_fail(e, "event record");

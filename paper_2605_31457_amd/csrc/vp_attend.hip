@@ -743,12 +743,15 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
 // Once per sequence in a launch with the visual role, by one wave: a new step's
 // arrival counters of the sequence's T*U selection rows at zero, and the
 // sequence's clipped segment table (positions and visual ranks) for the select
-// kernel. A wave of the sequence's last part of KV head 0 does it after its
-// tiles (the launch of one-wave work-groups has a work-group more for it).
+// kernel. A wave of the sequence's last part of KV head 0 does it (an extra
+// work-group would push the launch past one resident round: 52 -> 61 us at the
+// 8 x 10.8k batch of the 72B shape); the launch of one-wave work-groups, which
+// leaves a quarter of the slots free, has a work-group more for it.
+template <int D>
 __device__ __forceinline__ void step_setup(const AttendArgs& a, int b) {
   const int lane = threadIdx.x & 63;
-  if (a.sync)
-    for (int i = lane; i < a.T * a.U; i += 64) a.sync[static_cast<size_t>(b) * a.T * a.U + i] = 0u;
+  for (int i = lane; i < a.T * a.U; i += 64)
+    reinterpret_cast<uint32_t*>(a.kacc)[arrival_word(b, i / a.U, i % a.U, a.Hq, a.G, a.T, a.U, a.nsplit, D)] = 0u;
   if (a.segtab) {
     const int L = vis_len(clamp_len(a.seq_len[b], a.max_seq_len), a.T);
     const int o0 = a.seg_off[b];
@@ -768,6 +771,7 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
   using P = Pass<DT, D, MODE>;
   using Q = PassLds<DT, D, MODE, W>;
   constexpr int VB = Q::VB;
+  constexpr bool PAIRS = P::VIS && P::ATTN;  // two visual tiles per step
   unsigned char* lds = lds_block + wave * Q::BYTES;
   lds_byte* lds_dma = (lds_byte*)lds;  // the copies' view of it (converted once: a generic pointer may be null)
 
@@ -847,6 +851,16 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
                 ? a.zs + (static_cast<size_t>(b) * a.Hkv + g) * a.zs_rows * static_cast<size_t>(a.zs_gp) + qk * a.G
                 : nullptr;
 
+  // a wave of both roles needs its first tile's K rows whatever they are: they are
+  // requested before the segments are known
+  bool k_early = false;
+  if constexpr (PAIRS && !P::PAGED) {
+    k_early = s.even && s.r0 + 32 <= s.L;
+    if (k_early) s.copy_even_rows(s.Kb + static_cast<size_t>(s.r0) * s.rstride, lds_dma);
+  }
+  // the step setup waits for its loads in the shadow of the first tile's copies
+  bool setup = P::VIS && W > 1 && g == 0 && part == a.nparts - 1 && wave == W - 1;
+
   Sub cur;
   cur.t0 = s.r0;
   cur.cls = TILE_TEXT;
@@ -860,7 +874,6 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
   // or, with both roles, two visual tiles of the wave (the second one's K rows in
   // the block that holds a text tile's V rows), so that a wave has 16 KB in
   // flight whatever its tiles hold.
-  constexpr bool PAIRS = P::VIS && P::ATTN;
   while (cur.t0 < s.r1) {
     const Sub t0 = cur;
     const bool act = s.active(t0);
@@ -884,7 +897,8 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
       if constexpr (W > 1) unhoist_scalar(dma);
       if (!P::KEPT && s.even && t0.t0 + 32 <= s.L) {
         const size_t off = s.tile_offset(t0);
-        s.copy_even_rows(s.Kb + off, dma);
+        if (!k_early) s.copy_even_rows(s.Kb + off, dma);
+        k_early = false;
         if (s.needs_v(t0)) s.copy_even_rows(s.Vb + off, dma + C::SUB_ROWS_BYTES);
       } else {
         size_t off[C::COPIES];
@@ -907,6 +921,10 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
     }
     // the next step's kept positions / segment state load while these copies fly
     cur = s.sub_at(pair ? t1 : t0, (pair ? t1.t0 : t0.t0) + s.step);
+    if (setup) {
+      step_setup<D>(a, b);
+      setup = false;
+    }
     // the copies have landed in LDS once the vector-memory counter drains
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
     if (!act) continue;
@@ -944,7 +962,7 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
     }
   }
   if constexpr (W > 1) {
-    if (P::VIS && g == 0 && part == a.nparts - 1 && wave == W - 1) step_setup(a, b);
+    if (setup) step_setup<D>(a, b);  // a wave without tiles
     const float s_lt = P::TEXT ? sum_over_quads(s.l_t) : 0.f;
     const float s_lm = P::TSTATS ? sum_over_quads(s.Lm_t) : 0.f;
     const float s_ls = P::TSTATS ? (a.tau_s_one ? s_lt : sum_over_quads(s.Ls_t)) : 0.f;
@@ -978,7 +996,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(attend_waves
     const AttendArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[PassLds<DT, D, MODE, 1>::BYTES];
   if (base_mode(MODE) == MODE_VIS && static_cast<int>(blockIdx.x) == a.nparts) {
-    if (blockIdx.y == 0) step_setup(a, blockIdx.z);
+    if (blockIdx.y == 0) step_setup<D>(a, blockIdx.z);
     return;
   }
   attend_body<DT, D, MODE>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z);

@@ -324,7 +324,7 @@ __device__ __forceinline__ int lanes_below(uint64_t mask) {
 }
 
 struct SelectShared {
-  uint32_t hist[kHistWords];
+  alignas(16) uint32_t hist[kHistWords];
   alignas(16) int wcnt[kSelWaves];
   alignas(16) int gt[kSelWaves];
   alignas(16) int eq[kSelWaves];
@@ -376,7 +376,8 @@ __device__ __forceinline__ void block_key_range(SelectShared& sh, uint32_t& kmin
   }
 }
 
-// Radix select of the k-th largest of n keys (key_at(i)), 0 < k < n, whose
+// Radix select of the k-th largest of n keys, 0 < k < n (keys(f) calls f on
+// every key that this thread visits), whose
 // range is [kmin, kmax]: each pass histograms the surviving candidates on the
 // next 13 bits of (key - lo) into 8192 counters; a block suffix scan finds the
 // digit holding the k-th largest key and the live range shrinks to it. Digits
@@ -387,17 +388,16 @@ __device__ __forceinline__ void block_key_range(SelectShared& sh, uint32_t& kmin
 // keys are every key > T and the first `need` keys equal to T (need = 0 after
 // an early finish). sh.hist must be zero on entry (it is zero on exit).
 // Three barriers per pass; the owner of a counter clears it while scanning.
-template <typename KeyAt>
-__device__ __forceinline__ uint32_t radix_select(SelectShared& sh, KeyAt key_at, int n, int& need, uint32_t kmin,
+template <typename Keys>
+__device__ __forceinline__ uint32_t radix_select(SelectShared& sh, Keys keys, int& need, uint32_t kmin,
                                                  uint32_t kmax, int tid, int lane, int wid) {
   uint32_t lo = kmin;
   uint32_t span = kmax - kmin;  // candidates: lo <= key <= lo + span
   int shift = span == 0 ? 0 : max(0, 32 - __clz(static_cast<int>(span)) - kDigitBits);
   while (span != 0) {
-    for (int i = tid; i < n; i += kSelThreads) {
-      const uint32_t u = key_at(i);
+    keys([&](uint32_t u) {
       if (u >= lo && u - lo <= span) atomicAdd(&sh.hist[hslot(static_cast<int>((u - lo) >> shift))], 1u);
-    }
+    });
     __syncthreads();
     // thread t owns bins kBins-1-8t .. kBins-8-8t (descending): read and clear
     // them, then a block inclusive scan of the per-thread totals
@@ -516,5 +516,124 @@ __device__ __forceinline__ void ordered_compaction(SelectShared& sh, const SegTa
   }
 }
 
+// Keys held in registers, KPT per thread: wave w owns the ranks
+// [64 KPT w, 64 KPT (w + 1)), slot j of lane l is rank 64 (KPT w + j) + l. The
+// radix passes then read no memory, and the ordered compaction finds a wave's
+// kept ranks with one ballot per slot. Slots past n are masked.
+template <int KPT>
+struct RegKeys {
+  uint32_t u[KPT];
+  int r0;  // rank of slot 0
+  int n;
+  __device__ __forceinline__ int rank(int j) const { return r0 + 64 * j; }
+};
+
+// The ordered compaction above for keys in registers: the same output. What
+// bounds it is instruction issue (a SIMD runs four of the block's waves): a
+// first loop takes one ballot per slot and leaves it with lane j; the offsets of
+// the slots are a wave scan; then every lane walks only its own kept slots,
+// reading their ballots back from LDS (16384 ranks, 819 kept: 5.7 us for the
+// compaction with a full update of every slot by every wave).
+template <int KPT>
+__device__ __forceinline__ void ordered_compaction(SelectShared& sh, const SegTable& tab, const RegKeys<KPT>& keys,
+                                                   int k, int need, uint32_t T, bool take_all, int32_t* out, int lane,
+                                                   int wid) {
+  // ties (need > 0, keys == T kept up to a count): one more ballot per slot
+  const bool ties = need > 0 && !take_all;
+  uint64_t mgt = 0ull, meq = 0ull;  // lane j: slot j's keys > T, == T
+  uint32_t mine = 0u, tied = 0u;    // bit j: this lane's slot j is > T, == T
+#pragma unroll
+  for (int j = 0; j < KPT; ++j) {
+    const bool in = keys.rank(j) < keys.n;
+    const bool gt = in && (take_all || keys.u[j] > T);
+    const uint64_t b = __ballot(gt);
+    if (lane == j) mgt = b;
+    mine |= gt ? 1u << j : 0u;
+  }
+  if (ties) {
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+      const bool eq = keys.rank(j) < keys.n && keys.u[j] == T;
+      const uint64_t b = __ballot(eq);
+      if (lane == j) meq = b;
+      tied |= eq ? 1u << j : 0u;
+    }
+  }
+  // keys > T and == T in the wave's slots below lane j's
+  const int cg = __popcll(mgt), ce = __popcll(meq);
+  const int pg = wave_incl_sum(cg), pe = ties ? wave_incl_sum(ce) : 0;
+  if (lane == 63) {
+    sh.gt[wid] = pg;
+    sh.eq[wid] = pe;
+  }
+  // the radix counters are free now: per wave KPT ballots and offsets, then the staged ranks
+  uint4* slot = reinterpret_cast<uint4*>(sh.hist) + wid * KPT;
+  if (lane < KPT)
+    slot[lane] = make_uint4(static_cast<uint32_t>(mgt), static_cast<uint32_t>(mgt >> 32),
+                            static_cast<uint32_t>(pg - cg), 0u);
+  constexpr int kSlotWords = 4 * kSelWaves * KPT;
+  constexpr int kStage = kHistWords - kSlotWords;
+  static_assert(kStage > 0, "room for the staged ranks");
+  __syncthreads();
+  const int gt_run = waves_below(sh.gt, wid), eq_run = waves_below(sh.eq, wid);
+  const bool staged = k <= kStage;
+  uint32_t* stage = sh.hist + kSlotWords;
+  auto put = [&](int o, int j) {
+    if (o < k) {
+      if (staged) stage[o] = static_cast<uint32_t>(keys.rank(j));
+      else out[o] = rank_to_pos(tab, keys.rank(j));
+    }
+  };
+  if (!ties) {
+    while (mine) {
+      const int j = __builtin_ctz(mine);
+      mine &= mine - 1;
+      const uint4 s = slot[j];
+      put(gt_run + static_cast<int>(s.z) + lanes_below((static_cast<uint64_t>(s.y) << 32) | s.x), j);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {
+      // (every lane takes part in the shuffles)
+      const uint64_t bgt = __shfl(mgt, j), beq = __shfl(meq, j);
+      const int g_b = gt_run + __shfl(pg - cg, j) + lanes_below(bgt);
+      const int e_b = eq_run + __shfl(pe - ce, j) + lanes_below(beq);
+      const bool gt = (mine >> j) & 1u, eq = (tied >> j) & 1u;
+      if (gt || (eq && e_b < need)) put(g_b + min(need, e_b), j);
+    }
+  }
+  if (staged) {
+    __syncthreads();
+    for (int o = wid * 64 + lane; o < k; o += kSelThreads) out[o] = rank_to_pos(tab, static_cast<int>(stage[o]));
+  }
+}
+
+// Eq. (3) from keys in registers (0 < k <= n; take_all: k >= n), whose range is
+// [kmin, kmax]: the radix select, then the compaction.
+template <int KPT>
+__device__ __forceinline__ void select_from_registers(SelectShared& sh, const SegTable& tab, const RegKeys<KPT>& keys,
+                                                      int k, bool take_all, uint32_t kmin, uint32_t kmax, int32_t* out,
+                                                      int tid, int lane, int wid) {
+  uint32_t T = 0u;
+  int need = k;
+  if (!take_all)
+    T = radix_select(
+        sh,
+        [&](auto visit) {
+#pragma unroll
+          for (int j = 0; j < KPT; ++j)
+            if (keys.rank(j) < keys.n) visit(keys.u[j]);
+        },
+        need, kmin, kmax, tid, lane, wid);
+  ordered_compaction(sh, tab, keys, k, take_all ? 0 : need, T, take_all, out, lane, wid);
+}
+
+// keys per thread of the register path for rows of up to max_vis keys; 0: too
+// many, the keys stay in LDS or memory
+inline int reg_keys(int max_vis) {
+  for (int kpt = 2; kpt <= 32; kpt *= 2)
+    if (max_vis <= kpt * kSelThreads) return kpt;
+  return 0;
+}
 
 }  // namespace vp

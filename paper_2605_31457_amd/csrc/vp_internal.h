@@ -21,6 +21,15 @@ constexpr size_t kSegTableBytes = 3088;
 __host__ __device__ inline int vhead(int h, int t, int G, int T) { return (h / G) * (T * G) + t * G + h % G; }
 // positions visible as visual to the queries of a sequence of length L: the
 // last T - 1 positions are the other queries' tokens (text)
+// Arrival counter of selection row (b, t, u) in the select kernel: the first word
+// of the row's first head's kept-row partials [nsplit][d], which nothing uses
+// between the context pass (it zeroes the counters) and the kept pass. That
+// keeps every counter on a cache line of its own: packed counters serialised
+// the arrivals of all rows (16 rows x 16 chunks: 3.5 us from the scores to the
+// last arrival).
+__host__ __device__ inline size_t arrival_word(int b, int t, int u, int Hq, int G, int T, int U, int nsplit, int d) {
+  return (static_cast<size_t>(b) * T * Hq + vhead(u * (Hq / U), t, G, T)) * nsplit * d;
+}
 __host__ __device__ inline int vis_len(int L, int T) { return L - T + 1 > 0 ? L - T + 1 : 0; }
 
 // Waves that share a context-pass part when both roles run in one launch
@@ -47,7 +56,6 @@ struct Plan {
   size_t head;    // float [B][T*Hq][2]         merged (max, score normaliser)
   size_t kstats;  // float [B][T*Hq][nsplit][2] kept-row (max, sum)
   size_t kacc;    // float [B][T*Hq][nsplit][d] kept-row value partials
-  size_t sync;    // uint32 [B][T][U]           select-kernel arrival counters (per selection row)
   size_t segtab;  // SegTable [B]               clipped segment tables (positions, ranks)
   int sel_chunk;  // visual ranks scored per select work-group
   int sel_chunks; // select work-groups per selection row
@@ -111,7 +119,6 @@ struct AttendArgs {
   int k_cap, split, nsplit;
   float* kstats;
   float* kacc;
-  uint32_t* sync;       // [B][T][U] arrival counters of the select kernel (may be null)
   void* segtab;         // [B] segment tables (SegTable) for the select kernel (may be null)
 };
 
@@ -156,7 +163,8 @@ struct SelectArgs {
   int32_t* vis_idx;
   int chunk;       // visual ranks scored per work-group
   int nchunks;     // work-groups per selection row
-  uint32_t* sync;  // [B*T*U] arrival counters (nchunks > 1), zeroed by the context pass
+  float* kacc;     // the kept pass's partials: until it runs, they hold the rows' arrival counters
+  int nsplit, head_dim;
   const void* segtab;  // [B] segment tables written by the context pass
 };
 

@@ -123,8 +123,6 @@ Plan make_plan(const vp_shape& s) {
   p.kacc = off;
   off = align256(off + B * Hq * p.nsplit * d * 4);
   const size_t rows = B * static_cast<size_t>(rows_per_seq(s));
-  p.sync = off;
-  off = align256(off + rows * 4);
   p.segtab = off;
   off = align256(off + B * kSegTableBytes);
   p.total = off;

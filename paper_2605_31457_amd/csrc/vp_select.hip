@@ -42,8 +42,10 @@ __device__ __forceinline__ float load_score(const float* p) {
   return __hip_atomic_load(const_cast<float*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// GP: floats per spill row (the query group padded to 8 or 16)
-template <int GP>
+// GP: floats per spill row (the query group padded to 8 or 16). KPT > 0: the
+// selecting work-group holds the row's keys in registers (max_vis <= KPT *
+// kSelThreads); 0: in LDS (rows of up to lds_keys) or memory.
+template <int GP, int KPT>
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs t, int lds_keys) {
   extern __shared__ __attribute__((aligned(16))) unsigned char dyn[];
   __shared__ SelectShared sh;
@@ -140,7 +142,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs t,
       const float S = total / static_cast<float>(a.Hq / a.U);
       store_score(sc + i, S);
       const uint32_t u = order_key(S);
-      if (single && in_lds) s_keys[i] = u;
+      if (single && in_lds) s_keys[i] = u;  // (a single chunk's keys pass through LDS)
       kmin = min(kmin, u);
       kmax = max(kmax, u);
     }
@@ -159,6 +161,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs t,
     // block_key_range then puts them before any wave's reads.
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
   }
+  RegKeys<(KPT > 0 ? KPT : 1)> keys;
+  keys.r0 = wid * 64 * KPT + lane;
+  keys.n = n;
   if (!single) {
     // publish this chunk's scores and count in; the last work-group of the
     // row selects. Every wave waits for its own score stores to complete
@@ -168,7 +173,9 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs t,
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
     if (tid == 0) {
-      const bool last = __hip_atomic_fetch_add(t.sync + row, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+      uint32_t* arrived = reinterpret_cast<uint32_t*>(t.kacc) +
+                          arrival_word(b, qt, u, a.Hq, a.G, a.T, a.U, t.nsplit, t.head_dim);
+      const bool last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                         static_cast<unsigned>(t.nchunks - 1);
       s_last = last;
     }
@@ -176,8 +183,19 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs t,
     if (!s_last) return;
     kmin = 0xffffffffu;
     kmax = 0u;
+    if constexpr (KPT > 0) {
+      float v[KPT];
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) v[j] = load_score(sc + max(0, min(keys.rank(j), n - 1)));
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) {  // slots past n hold the last key: no change of the range
+        keys.u[j] = order_key(v[j]);
+        kmin = min(kmin, keys.u[j]);
+        kmax = max(kmax, keys.u[j]);
+      }
+    }
     constexpr int kBatch = 8;  // loads in flight per thread
-    for (int base = 0; base < n; base += kBatch * kSelThreads) {
+    for (int base = 0; KPT == 0 && base < n; base += kBatch * kSelThreads) {
       float v[kBatch];
 #pragma unroll
       for (int j = 0; j < kBatch; ++j) v[j] = load_score(sc + min(base + j * kSelThreads + tid, n - 1));
@@ -195,6 +213,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs t,
   }
 
   // ---- Eq. (7) budget, then Eq. (3) selection ----
+  block_key_range(sh, kmin, kmax, lane, wid);  // (its barrier also publishes the head max)
   const int kb = budget_rule(static_cast<double>(hs.mseq[1]), nvis, t.r_lo_bp, t.r_hi_bp, t.clamp);
   if (tid == 0) t.k[row] = kb;
   int k = kb > n ? n : kb;
@@ -202,22 +221,35 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const SelectArgs t,
   int32_t* out = t.vis_idx + static_cast<size_t>(row) * t.k_cap;
   for (int i = k + tid; i < t.k_cap; i += kSelThreads) out[i] = -1;
   if (k == 0) return;
-  auto key_at = [&](int i) -> uint32_t { return in_lds ? s_keys[i] : order_key(load_score(sc + i)); };
   const bool take_all = k >= n;
-  uint32_t T = 0u;
-  int need = k;
-  block_key_range(sh, kmin, kmax, lane, wid);
-  if (!take_all) T = radix_select(sh, key_at, n, need, kmin, kmax, tid, lane, wid);
-  ordered_compaction(sh, tab, key_at, n, k, need, T, take_all, out, lane, wid);
+  if constexpr (KPT > 0) {
+    if (single) {
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) keys.u[j] = keys.rank(j) < n ? s_keys[keys.rank(j)] : 0u;
+    }
+    select_from_registers(sh, tab, keys, k, take_all, kmin, kmax, out, tid, lane, wid);
+  } else {
+    auto key_at = [&](int i) -> uint32_t { return in_lds ? s_keys[i] : order_key(load_score(sc + i)); };
+    uint32_t T = 0u;
+    int need = k;
+    if (!take_all)
+      T = radix_select(
+          sh,
+          [&](auto visit) {
+            for (int i = tid; i < n; i += kSelThreads) visit(key_at(i));
+          },
+          need, kmin, kmax, tid, lane, wid);
+    ordered_compaction(sh, tab, key_at, n, k, need, T, take_all, out, lane, wid);
+  }
 }
 
 // LDS per work-group beyond the kernel's static arrays, and the keys it leaves
 // room for (one GPU model per process is assumed: computed once)
-template <int GP>
+template <int GP, int KPT>
 int key_room(int Hq) {
   static const int stat = [] {
     hipFuncAttributes attr;
-    return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(select_kernel<GP>)) == hipSuccess
+    return hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(select_kernel<GP, KPT>)) == hipSuccess
                ? static_cast<int>(attr.sharedSizeBytes)
                : 48 * 1024;
   }();
@@ -231,16 +263,31 @@ int key_room(int Hq) {
   return max(0, max_lds - stat - head_lds_bytes(Hq) - 64) / 4;
 }
 
-template <int GP>
-hipError_t launch_gp(const SelectArgs& t, hipStream_t st) {
-  const int room = key_room<GP>(t.m.Hq);
+template <int GP, int KPT>
+hipError_t launch_keys(const SelectArgs& t, hipStream_t st) {
+  const int room = key_room<GP, KPT>(t.m.Hq);
   // keys of up to `room` visual ranks stay in LDS; a row with more reads its
-  // scores back from memory during the selection
-  const int keys = min(room, t.m.max_vis);
+  // scores back from memory during the selection. With the keys in registers
+  // only a single chunk's pass through LDS.
+  const int keys = KPT > 0 && t.nchunks > 1 ? 0 : min(room, t.m.max_vis);
   const size_t dyn = static_cast<size_t>(head_lds_bytes(t.m.Hq)) + static_cast<size_t>(keys) * 4;
-  hipLaunchKernelGGL((select_kernel<GP>), dim3(t.nchunks, t.m.B * t.m.T * t.m.U), dim3(kSelThreads), dyn, st, t,
+  hipLaunchKernelGGL((select_kernel<GP, KPT>), dim3(t.nchunks, t.m.B * t.m.T * t.m.U), dim3(kSelThreads), dyn, st, t,
                      keys);
   return hipGetLastError();
+}
+
+template <int GP>
+hipError_t launch_gp(const SelectArgs& t, hipStream_t st) {
+  // a single chunk whose keys would not fit LDS takes the general path
+  const int kpt = t.nchunks == 1 && key_room<GP, 32>(t.m.Hq) < t.m.max_vis ? 0 : reg_keys(t.m.max_vis);
+  switch (kpt) {
+    case 2: return launch_keys<GP, 2>(t, st);
+    case 4: return launch_keys<GP, 4>(t, st);
+    case 8: return launch_keys<GP, 8>(t, st);
+    case 16: return launch_keys<GP, 16>(t, st);
+    case 32: return launch_keys<GP, 32>(t, st);
+    default: return launch_keys<GP, 0>(t, st);
+  }
 }
 
 }  // namespace

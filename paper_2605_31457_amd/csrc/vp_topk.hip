@@ -25,6 +25,9 @@
 namespace vp {
 namespace {
 
+// KPT > 0: the row's keys in registers (max_vis <= KPT * kSelThreads); 0: in LDS
+// (the first lds_keys of them fit) or read from memory on every sweep
+template <int KPT>
 __global__ __launch_bounds__(kSelThreads) void topk_kernel(const TopkArgs a, int lds_keys) {
   extern __shared__ uint32_t s_keys[];
   __shared__ SelectShared sh;
@@ -54,8 +57,27 @@ __global__ __launch_bounds__(kSelThreads) void topk_kernel(const TopkArgs a, int
   for (int i = k + tid; i < a.k_cap; i += kSelThreads) out[i] = -1;
   if (k == 0) return;
   const float* sc = a.scores + static_cast<size_t>(row) * a.max_vis;
-  const bool in_lds = n <= lds_keys;
   const bool take_all = k >= n;
+  if constexpr (KPT > 0) {
+    for (int i = tid; i < kHistWords; i += kSelThreads) sh.hist[i] = 0;
+    RegKeys<KPT> keys;
+    keys.r0 = wid * 64 * KPT + lane;
+    keys.n = n;
+    float v[KPT];
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) v[j] = sc[min(keys.rank(j), n - 1)];
+    uint32_t kmin = 0xffffffffu, kmax = 0u;
+#pragma unroll
+    for (int j = 0; j < KPT; ++j) {  // slots past n hold the last key: no change of the range
+      keys.u[j] = order_key(v[j]);
+      kmin = min(kmin, keys.u[j]);
+      kmax = max(kmax, keys.u[j]);
+    }
+    block_key_range(sh, kmin, kmax, lane, wid);
+    select_from_registers(sh, tab, keys, k, take_all, kmin, kmax, out, tid, lane, wid);
+    return;
+  }
+  const bool in_lds = n <= lds_keys;
   auto key_at = [&](int i) -> uint32_t { return in_lds ? s_keys[i] : order_key(sc[i]); };
 
   uint32_t T = 0u;
@@ -85,7 +107,12 @@ __global__ __launch_bounds__(kSelThreads) void topk_kernel(const TopkArgs a, int
     }
     block_key_range(sh, kmin, kmax, lane, wid);
     // ---- 2. radix select of the k-th largest key ----
-    T = radix_select(sh, key_at, n, need, kmin, kmax, tid, lane, wid);
+    T = radix_select(
+        sh,
+        [&](auto visit) {
+          for (int i = tid; i < n; i += kSelThreads) visit(key_at(i));
+        },
+        need, kmin, kmax, tid, lane, wid);
   }
   // ---- 3. ordered compaction ----
   ordered_compaction(sh, tab, key_at, n, k, need, T, take_all, out, lane, wid);
@@ -296,6 +323,15 @@ hipError_t launch_top_p(const TopPArgs& a, hipStream_t st) {
 }
 
 hipError_t launch_topk(const TopkArgs& a, hipStream_t st) {
+  const dim3 grid(a.B * a.R);
+  switch (reg_keys(a.max_vis)) {
+    case 2: hipLaunchKernelGGL(topk_kernel<2>, grid, dim3(kSelThreads), 0, st, a, 0); return hipGetLastError();
+    case 4: hipLaunchKernelGGL(topk_kernel<4>, grid, dim3(kSelThreads), 0, st, a, 0); return hipGetLastError();
+    case 8: hipLaunchKernelGGL(topk_kernel<8>, grid, dim3(kSelThreads), 0, st, a, 0); return hipGetLastError();
+    case 16: hipLaunchKernelGGL(topk_kernel<16>, grid, dim3(kSelThreads), 0, st, a, 0); return hipGetLastError();
+    case 32: hipLaunchKernelGGL(topk_kernel<32>, grid, dim3(kSelThreads), 0, st, a, 0); return hipGetLastError();
+    default: break;
+  }
   // dynamic LDS left for staged keys after the kernel's static arrays (one GPU
   // model per process is assumed: the figure is computed once)
   static const int lds_room = [] {
@@ -304,13 +340,13 @@ hipError_t launch_topk(const TopkArgs& a, hipStream_t st) {
         hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
       max_lds = 65536;
     hipFuncAttributes attr;
-    const int stat = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(topk_kernel)) == hipSuccess
+    const int stat = hipFuncGetAttributes(&attr, reinterpret_cast<const void*>(topk_kernel<0>)) == hipSuccess
                          ? static_cast<int>(attr.sharedSizeBytes)
                          : 48 * 1024;
     return max(0, max_lds - stat - 64);
   }();
   const int keys = min(lds_room / 4, a.max_vis);
-  hipLaunchKernelGGL(topk_kernel, dim3(a.B * a.R), dim3(kSelThreads), static_cast<size_t>(keys) * 4, st, a, keys);
+  hipLaunchKernelGGL(topk_kernel<0>, grid, dim3(kSelThreads), static_cast<size_t>(keys) * 4, st, a, keys);
   return hipGetLastError();
 }
 
