@@ -643,10 +643,11 @@ struct WaveStats {
 
 // Merges the partials of a work-group's W waves (every wave calls it, waves
 // without tiles included, with m = -inf and sums of zero) and writes the part's
-// statistics and attention partial: maxima and sums meet in LDS (the sums in
-// double), each wave rescales its accumulator to the common maximum and leaves
-// it in its own LDS block (rows padded by four floats: consecutive heads start
-// on different banks), and the block adds the W copies in wave order.
+// statistics and attention partial. Each wave leaves its maxima, sums and
+// accumulator in LDS (accumulator rows padded by four floats: consecutive heads
+// start on different banks); after the one barrier wave 0 merges the visual
+// statistics and the last wave the text ones (sums in double), and the block adds the W
+// accumulators in wave order, each rescaled to the common maximum.
 template <int DT, int D, int MODE, int W>
 __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, MODE>& s, WaveStats<W>& ws,
                                               unsigned char* lds, int wave, int part, int g, int b, float m_v,
@@ -669,48 +670,44 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
       o[6] = ls_t;
     }
   }
-  __syncthreads();
-  float M = kNegInf;
-  if constexpr (P::TEXT) {
-#pragma unroll
-    for (int w = 0; w < W; ++w) M = fmaxf(M, ws.v[w][s.n16][3]);
-  }
-  if constexpr (P::ATTN) {
-    const float f = s.m_t == kNegInf ? 0.f : fast_exp2(s.m_t - M);
-#pragma unroll
-    for (int i = 0; i < C::ACC_N; ++i) s.acc[i] *= f;
+  if constexpr (P::ATTN)
     store_acc<DT, D, C::ACC_N>(reinterpret_cast<float*>(lds + wave * PassLds<DT, D, MODE, W>::BYTES) + s.n16 * PITCH,
                                s.acc, s.a4);
-  }
-  const size_t head0 = static_cast<size_t>(b) * a.T * a.Hq + static_cast<size_t>(g) * a.T * a.G;
-  if (wave == 0 && s.a4 == 0 && s.hv) {
-    float* st = a.stats + ((head0 + s.n16) * a.nparts + part) * 8;
-    if constexpr (P::VIS) {
-      float Mv = kNegInf;
+  __syncthreads();
+  // weight of wave w's sums after the rescaling of column c (a maximum) of head h by 1/tau
+  auto top = [&](int h, int c) {
+    float M = kNegInf;
 #pragma unroll
-      for (int w = 0; w < W; ++w) Mv = fmaxf(Mv, ws.v[w][s.n16][0]);
+    for (int w = 0; w < W; ++w) M = fmaxf(M, ws.v[w][h][c]);
+    return M;
+  };
+  auto weight = [&](int w, int h, int c, float M, float inv_tau) {
+    const float m = ws.v[w][h][c];
+    return m == kNegInf ? 0.f : fast_exp2((m - M) * inv_tau);
+  };
+  const size_t head0 = static_cast<size_t>(b) * a.T * a.Hq + static_cast<size_t>(g) * a.T * a.G;
+  if (s.a4 == 0 && s.hv) {
+    const int h = s.n16;
+    float* st = a.stats + ((head0 + h) * a.nparts + part) * 8;
+    if (P::VIS && wave == 0) {
+      const float M = top(h, 0);
       double ls = 0.0, lm = 0.0;
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        const float* o = ws.v[w][s.n16];
-        if (o[0] != kNegInf) {
-          ls += static_cast<double>(fast_exp2((o[0] - Mv) * a.inv_tau_s)) * o[1];
-          lm += static_cast<double>(fast_exp2((o[0] - Mv) * a.inv_tau_m)) * o[2];
-        }
+        ls += static_cast<double>(weight(w, h, 0, M, a.inv_tau_s)) * ws.v[w][h][1];
+        lm += static_cast<double>(weight(w, h, 0, M, a.inv_tau_m)) * ws.v[w][h][2];
       }
-      *reinterpret_cast<float4*>(st) = make_float4(Mv, static_cast<float>(ls), static_cast<float>(lm), 0.f);
+      *reinterpret_cast<float4*>(st) = make_float4(M, static_cast<float>(ls), static_cast<float>(lm), 0.f);
     }
-    if constexpr (P::TEXT) {
+    if (P::TEXT && wave == W - 1) {
+      const float M = top(h, 3);
       double l = 0.0, lm = 0.0, ls = 0.0;
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        const float* o = ws.v[w][s.n16];
-        if (o[3] != kNegInf) {
-          l += static_cast<double>(fast_exp2(o[3] - M)) * o[4];
-          if constexpr (P::TSTATS) {
-            lm += static_cast<double>(fast_exp2((o[3] - M) * a.inv_tau_m)) * o[5];
-            ls += static_cast<double>(fast_exp2((o[3] - M) * a.inv_tau_s)) * o[6];
-          }
+        l += static_cast<double>(weight(w, h, 3, M, 1.f)) * ws.v[w][h][4];
+        if constexpr (P::TSTATS) {
+          lm += static_cast<double>(weight(w, h, 3, M, a.inv_tau_m)) * ws.v[w][h][5];
+          ls += static_cast<double>(weight(w, h, 3, M, a.inv_tau_s)) * ws.v[w][h][6];
         }
       }
       if constexpr (P::TSTATS)
@@ -721,19 +718,20 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
     }
   }
   if constexpr (P::ATTN) {
-    __syncthreads();
     constexpr int COLS = D / 4;
     for (int i = threadIdx.x; i < a.T * a.G * COLS; i += 64 * W) {
       const int h = i / COLS, c = i % COLS;
+      const float M = top(h, 3);
       float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int w = 0; w < W; ++w) {
+        const float f = weight(w, h, 3, M, 1.f);
         const float4 x = reinterpret_cast<const float4*>(
             reinterpret_cast<const float*>(lds + w * PassLds<DT, D, MODE, W>::BYTES) + h * PITCH)[c];
-        t.x += x.x;
-        t.y += x.y;
-        t.z += x.z;
-        t.w += x.w;
+        t.x = fmaf(f, x.x, t.x);
+        t.y = fmaf(f, x.y, t.y);
+        t.z = fmaf(f, x.z, t.z);
+        t.w = fmaf(f, x.w, t.w);
       }
       reinterpret_cast<float4*>(a.acc + ((head0 + h) * a.nparts + part) * D)[c] = t;
     }
@@ -743,10 +741,12 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
 // Once per sequence in a launch with the visual role, by one wave: a new step's
 // arrival counters of the sequence's T*U selection rows at zero, and the
 // sequence's clipped segment table (positions and visual ranks) for the select
-// kernel. A wave of the sequence's last part of KV head 0 does it (an extra
-// work-group would push the launch past one resident round: 52 -> 61 us at the
-// 8 x 10.8k batch of the 72B shape); the launch of one-wave work-groups, which
-// leaves a quarter of the slots free, has a work-group more for it.
+// kernel. It has a work-group of its own where the launch leaves slots free (the
+// one-wave passes, small steps); in a launch that fills the GPU a wave of the
+// sequence's last part of KV head 0 does it (there, extra work-groups push the
+// launch past one resident round: 52 -> 61 us at the 8 x 10.8k batch of the 72B
+// shape; in a small step, that wave is on the critical path: the fp32 step of 384
+// tokens 23.4 -> 24.4 us).
 template <int D>
 __device__ __forceinline__ void step_setup(const AttendArgs& a, int b) {
   const int lane = threadIdx.x & 63;
@@ -859,7 +859,8 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
     if (k_early) s.copy_even_rows(s.Kb + static_cast<size_t>(s.r0) * s.rstride, lds_dma);
   }
   // the step setup waits for its loads in the shadow of the first tile's copies
-  bool setup = P::VIS && W > 1 && g == 0 && part == a.nparts - 1 && wave == W - 1;
+  bool setup = P::VIS && W > 1 && static_cast<int>(gridDim.x) == a.nparts && g == 0 && part == a.nparts - 1 &&
+               wave == W - 1;
 
   Sub cur;
   cur.t0 = s.r0;
@@ -1015,6 +1016,10 @@ attend_waves_kernel(const AttendArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[W * PassLds<DT, D, MODE, W>::BYTES];
   __shared__ WaveStats<W> ws;
   const int wave = wave_index();
+  if (static_cast<int>(blockIdx.x) == a.nparts) {
+    if (wave == 0 && blockIdx.y == 0) step_setup<D>(a, blockIdx.z);
+    return;
+  }
   attend_body<DT, D, MODE, W>(a, lds, blockIdx.x, blockIdx.y, blockIdx.z, wave, &ws);
 }
 
@@ -1085,7 +1090,9 @@ template <int DT, int D, int PG>
 hipError_t launch_waves(const AttendArgs& a, int mode, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   constexpr int W = kPartWaves;
   int gx = a.nparts;
-  if (mode == MODE_TEXT_KEPT) gx = a.nparts + (a.T * a.nsplit + W - 1) / W;
+  if ((mode & MODE_VIS) != 0 && static_cast<int64_t>(a.nparts + 1) * a.Hkv * a.B * W <= kResidentWaves)
+    gx = a.nparts + 1;  // room for the step setup's own work-groups
+  else if (mode == MODE_TEXT_KEPT) gx = a.nparts + (a.T * a.nsplit + W - 1) / W;
   const dim3 grid(gx, a.Hkv, a.B);
   switch (mode) {
     case MODE_TEXT_ATTN:  // the text parts alone

@@ -50,7 +50,8 @@ __device__ __forceinline__ int lanes_per_head(int Hq, int nparts) {
 // rows, kept apart by the context pass) for every head of selection row u of
 // the query (heads [u Hq/U, (u+1) Hq/U)) onto the head's maximum, in
 // double with fixed-order reductions, by a kSelThreads block (every thread
-// calls it; two block barriers). Every head gets a group of lanes (a power of
+// calls it; one block barrier, after which the per-head results are in `hs`; the
+// head mean and max are there after the caller's next barrier). Every head gets a group of lanes (a power of
 // two, lanes_per_head of the row's head count; one round of heads since Hq <= kSelThreads) that
 // strides over the parts and reduces on the DPP network. When the part capacity allows, each lane's (up to four) parts are
 // requested at entry at addresses that do not depend on the sequence length,
@@ -183,17 +184,17 @@ __device__ __forceinline__ void reduce_heads(const MassArgs& a, int b, int qt, i
     }
   }
   __syncthreads();
-  // head mean and head max of the row: lane j takes heads h0 + j, h0 + j + 64,
-  // ... in order, then a fixed butterfly
-  if (tid < 64) {
+  // head mean and head max of the row by the last wave, while the others go on:
+  // lane j takes heads h0 + j, h0 + j + 64, ... in order, then a fixed butterfly
+  if (tid >= kSelThreads - 64) {
     double msum = 0.0, mmax = 0.0;
-    for (int hh = h0 + tid; hh < h0 + Hu; hh += 64) {
+    for (int hh = h0 + (tid & 63); hh < h0 + Hu; hh += 64) {
       msum += hs.mass[hh];
       mmax = hs.mass[hh] > mmax ? hs.mass[hh] : mmax;
     }
     msum = group_sum_f64(msum, 64);
     mmax = group_max_f64(mmax, 64);
-    if (tid == 0) {
+    if ((tid & 63) == 0) {
       const float mv = static_cast<float>(msum / Hu);
       const float mx = static_cast<float>(mmax);
       hs.mseq[0] = mv;
@@ -205,7 +206,6 @@ __device__ __forceinline__ void reduce_heads(const MassArgs& a, int b, int qt, i
       }
     }
   }
-  __syncthreads();
 }
 
 // One head's term of the Eq. (2) score of a visual token: s + 2^((z - m)/tau) / Ls,

@@ -38,6 +38,9 @@ __host__ __device__ inline int vis_len(int L, int T) { return L - T + 1 > 0 ? L 
 #endif
 constexpr int kPartWaves = VP_PART_WAVES;
 
+// One resident round of the passes that read V: 8 waves per CU x 256 CUs
+constexpr int kResidentWaves = 2048;
+
 // Work decomposition and workspace carving, a pure function of the shape.
 struct Plan {
   int nparts;   // context-pass work-groups per (sequence, KV head); part p takes
