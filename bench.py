@@ -625,7 +625,7 @@ def main():
         "step_achieved_GBps": step_gbs,
         "step_frac_of_peak": step_gbs / PEAK_HBM_GBS,
         "gpu_event_ms_per_step": gpu_ms / steps,
-        "roofline": {"kernel": (f"context pass, one launch (attend_dual_kernel<{w.dtype},{w.d}>: visual K and "
+        "roofline": {"kernel": (f"context pass, one launch (attend_waves_kernel<{w.dtype},{w.d}>: visual K and "
                                 "text K/V, Eq. (6)/(5)/(2) statistics, logit spill, attention partial)")
                      if one_launch else
                      (f"text pass (attend_kernel<{w.dtype},{w.d},MODE_TEXT_BOTH>: text K/V, "

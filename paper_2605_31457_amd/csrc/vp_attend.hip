@@ -3,7 +3,9 @@
 // vp_sparse_decode_attn (Sec. 4.1/4.2).
 //
 // Work decomposition: one 64-lane wave per work-group; grid = (parts, Hkv, B)
-// (kept pass: (splits, Hkv * T, B), one row of work-groups per query).
+// (kept pass: (splits, Hkv * T, B), one row of work-groups per query). Up to
+// mid-size caches kPartWaves waves share a part, each with the visual and the
+// text role, and merge their partials in LDS (attend_waves_kernel).
 // In the context pass part p of `nparts` takes the 32-row tiles p, p + nparts,
 // p + 2 nparts, ... of the cache (a cyclic deal: every part, and so every XCD,
 // sees the sequence's own mix of visual and text rows); in the kept pass a part

@@ -19,8 +19,6 @@ constexpr size_t kSegTableBytes = 3088;
 // the group), so one pass over a KV head's rows serves all of them. Per-head
 // workspace arrays are indexed by virtual head: b*T*Hq + g*T*G + t*G + j.
 __host__ __device__ inline int vhead(int h, int t, int G, int T) { return (h / G) * (T * G) + t * G + h % G; }
-// positions visible as visual to the queries of a sequence of length L: the
-// last T - 1 positions are the other queries' tokens (text)
 // Arrival counter of selection row (b, t, u) in the select kernel: the first word
 // of the row's first head's kept-row partials [nsplit][d], which nothing uses
 // between the context pass (it zeroes the counters) and the kept pass. That
@@ -30,6 +28,8 @@ __host__ __device__ inline int vhead(int h, int t, int G, int T) { return (h / G
 __host__ __device__ inline size_t arrival_word(int b, int t, int u, int Hq, int G, int T, int U, int nsplit, int d) {
   return (static_cast<size_t>(b) * T * Hq + vhead(u * (Hq / U), t, G, T)) * nsplit * d;
 }
+// positions visible as visual to the queries of a sequence of length L: the
+// last T - 1 positions are the other queries' tokens (text)
 __host__ __device__ inline int vis_len(int L, int T) { return L - T + 1 > 0 ? L - T + 1 : 0; }
 
 // Waves that share a context-pass part when both roles run in one launch

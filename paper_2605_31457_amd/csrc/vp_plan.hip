@@ -15,7 +15,11 @@ int rows_per_query(const vp_shape& s) { return s.scope == VP_SCOPE_KV_GROUP ? s.
 int rows_per_seq(const vp_shape& s) { return queries(s) * rows_per_query(s); }
 
 // Waves of the one launch of both passes: one resident round (8 waves per CU x
-// 256 CUs), so no work-group waits for a second round.
+// 256 CUs), so no work-group waits for a second round, shared by kPartWaves
+// waves per part: a part's statistics and value partial are written once for
+// four waves, where one wave per part and role left the select and merge
+// launches 256 partials per head to read at one 30k-token sequence (per pass
+// 61.8 -> 49.2 us there, 80.5 -> 76.5 at the ragged 16-sequence batch).
 #ifndef VP_ONE_LAUNCH_WAVES
 #define VP_ONE_LAUNCH_WAVES 2048
 #endif
@@ -23,7 +27,7 @@ int rows_per_seq(const vp_shape& s) { return queries(s) * rows_per_query(s); }
 #define VP_ONE_LAUNCH_TILES 1  // 32-row tiles per wave of the one launch, at least
 #endif
 // The visual and text passes in two launches (large caches) take three
-// quarters of that: 6 parts per KV head at the 64 x 32k batch, where 4, 5, 6,
+// quarters of that, one wave each: 6 parts per KV head at the 64 x 32k batch, where 4, 5, 6,
 // 7 and 8 parts measured 660, 631, 613.6, 618.5 and 616.5 us per step (the
 // visual pass 265 / 238 / 222 / 226 / 225 us; the text pass 328.5 us at 4 parts
 // and within 1 us of 325 us at 5 to 8).
@@ -37,8 +41,8 @@ int rows_per_seq(const vp_shape& s) { return queries(s) * rows_per_query(s); }
 // Both context passes in one launch: saves a launch and overlaps the two
 // passes' latency chains where the cache is small; kept apart otherwise, so
 // the visual pass's logit writes stay out of the text pass's read stream.
-// Measured: the 8 x 10.5k batch of the 72B shape (22k tiles) gains 6 us from the
-// one launch with half the parts; the 64 x 32k batch (262k tiles) loses 100 us.
+// Measured with one wave per part: the 8 x 10.5k batch of the 72B shape (22k
+// tiles) gained 6 us from the one launch; the 64 x 32k batch (262k tiles) lost 100 us.
 #ifndef VP_DUAL_MAX_TILES
 #define VP_DUAL_MAX_TILES 32768  // 32-row tiles over the batch and KV heads
 #endif
@@ -61,14 +65,12 @@ bool use_dual(const vp_shape* s) {
 
 Plan make_plan(const vp_shape& s) {
   Plan p{};
-  // Context pass: about VP_TARGET_PARTS one-wave work-groups in all, each
-  // with at least two 32-row tiles. Tiles are dealt out cyclically, so every
-  // part sees the sequence's own mix of visual and text rows: consecutive
+  // Context pass: parts of kPartWaves waves (one launch) or one wave (two
+  // launches). Tiles are dealt out cyclically, so every part sees the sequence's own mix of visual and text rows: consecutive
   // work-groups land on different XCDs, and contiguous chunks would hand whole
   // XCDs only visual (K) or only text (K + V) rows.
   const int64_t pairs = static_cast<int64_t>(s.batch) * s.n_kv_heads;
   const int64_t tiles = (s.max_seq_len + 31) / 32;
-  // the one-launch context pass runs a visual and a text work-group per part
   const bool one_launch = use_dual(&s);
   p.waves = one_launch ? kPartWaves : 1;
   const int64_t min_tiles = one_launch ? kPartWaves * VP_ONE_LAUNCH_TILES : VP_MIN_TILES;
