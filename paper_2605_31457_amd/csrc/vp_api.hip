@@ -269,7 +269,7 @@ MergeArgs merge_args(const vp_shape* s, const Plan& plan, const AttendArgs& a, v
   m.Hq = s->n_q_heads;
   m.G = s->n_q_heads / s->n_kv_heads;
   m.T = queries(*s);
-  m.nparts = plan.nparts;
+  m.nparts = a.nparts;
   m.nsplit = plan.nsplit;
   m.seq_len = a.seq_len;
   m.vis_idx = a.vis_idx;
@@ -613,6 +613,10 @@ vp_status vp_sparse_decode_attn(const vp_shape* shape, const vp_layout* layout, 
     if (hipError_t e = launch_merge_kept(merge_args(shape, plan, a, out), shape->head_dim, st))
       return hip_fail(e, "merge launch");
     return VP_OK;
+  }
+  if (!(flags & VP_ATTN_TEXT_FROM_WORKSPACE)) {
+    a.nparts = plan.text_parts;
+    a.waves = plan.text_waves;
   }
   if (!(flags & VP_ATTN_TEXT_FROM_WORKSPACE) && plan.text_kept_one_launch) {
     // a layer that reads its own text rows: the text and kept passes share one launch

@@ -48,14 +48,16 @@ struct Plan {
   int waves;    // waves per context-pass work-group (kPartWaves, or 1 with the passes in two launches)
   int split;    // kept rows per kept-pass work-group (multiple of 32)
   int nsplit;   // ceil(k_cap / split)
+  int text_parts;  // parts and waves of the text pass that a later layer runs for itself
+  int text_waves;
   bool text_kept_one_launch;  // a later layer's text and kept passes fit one resident round together
   bool merge_kept;            // the step folds the kept rows into the merge (no kept pass)
   int zs_rows;    // rows per spill plane: max_seq_len rounded up to 32
   int zs_gp;      // floats per spill row: the query group padded to 8 or 16
   size_t zs;      // float [B][Hkv][zs_rows][zs_gp]  visual logits (log2 domain) by cache position
-  size_t stats;   // float [B][T*Hq][nparts][8] per-part statistics (by virtual head): visual rows
+  size_t stats;   // float [B][T*Hq][parts][8]  per-part statistics (by virtual head): visual rows
                   //   {m_v, Ls_v, Lm_v, -}, text rows {m_t, l_t, Lm_t, Ls_t}
-  size_t acc;     // float [B][T*Hq][nparts][d] per-part text value partials
+  size_t acc;     // float [B][T*Hq][parts][d]  per-part text value partials (room for nparts or text_parts)
   size_t head;    // float [B][T*Hq][2]         merged (max, score normaliser)
   size_t kstats;  // float [B][T*Hq][nsplit][2] kept-row (max, sum)
   size_t kacc;    // float [B][T*Hq][nsplit][d] kept-row value partials

@@ -2,6 +2,8 @@
 // the workspace is carved, a pure function of the shape (vp_shape). Kept apart
 // from the ABI's validation code: these choices, with the kernels, set what
 // the passes read and write.
+#include <algorithm>
+
 #include "vp_internal.h"
 
 namespace vp {
@@ -25,6 +27,9 @@ int rows_per_seq(const vp_shape& s) { return queries(s) * rows_per_query(s); }
 #endif
 #ifndef VP_ONE_LAUNCH_TILES
 #define VP_ONE_LAUNCH_TILES 1  // 32-row tiles per wave of the one launch, at least
+#endif
+#ifndef VP_LATER_TEXT_WAVES
+#define VP_LATER_TEXT_WAVES 1024  // waves of a later layer's text pass with single-wave parts
 #endif
 // The visual and text passes in two launches (large caches) take three
 // quarters of that, one wave each: 6 parts per KV head at the 64 x 32k batch, where 4, 5, 6,
@@ -74,10 +79,23 @@ Plan make_plan(const vp_shape& s) {
   const bool one_launch = use_dual(&s);
   p.waves = one_launch ? kPartWaves : 1;
   const int64_t min_tiles = one_launch ? kPartWaves * VP_ONE_LAUNCH_TILES : VP_MIN_TILES;
-  int64_t parts = one_launch ? VP_ONE_LAUNCH_WAVES / (kPartWaves * pairs) : (VP_TWO_LAUNCH_PARTS + pairs - 1) / pairs;
-  if (parts > (tiles + min_tiles - 1) / min_tiles) parts = (tiles + min_tiles - 1) / min_tiles;
-  if (parts < 1) parts = 1;
-  p.nparts = static_cast<int>(parts);
+  auto capped = [&](int64_t n, int64_t least) {
+    return static_cast<int>(std::max<int64_t>(1, std::min(n, (tiles + least - 1) / least)));
+  };
+  // rounded down (a second round of 72 to 192 (sequence, KV head) pairs measured
+  // 1.09 to 1.12 times the step), except that one part per pair would leave up to
+  // half of the GPU idle: two parts there (264 pairs of 3.7k tokens 125.2 -> 121.7
+  // us per step, 288 of head_dim 64 72.5 -> 65.2, 504 104.4 -> 102.7; 384 105.6 -> 108.6)
+  constexpr int64_t kRound = VP_ONE_LAUNCH_WAVES / kPartWaves;
+  const bool many_pairs = one_launch && pairs > kRound / 2;
+  p.nparts = !one_launch ? capped((VP_TWO_LAUNCH_PARTS + pairs - 1) / pairs, min_tiles)
+                         : capped(many_pairs && pairs < kRound ? 2 : kRound / pairs, min_tiles);
+  // A later layer's text pass has the context pass's parts, but with many pairs
+  // single-wave parts, one to four per pair: they balance the text rows alone
+  // better (a later layer with four-wave parts and here: 68.1 and 64.8 us at 264
+  // pairs, 56.0 and 50.9 at 288, 52.3 and 47.3 at 1024)
+  p.text_waves = many_pairs ? 1 : p.waves;
+  p.text_parts = many_pairs ? capped((VP_LATER_TEXT_WAVES + pairs - 1) / pairs, VP_MIN_TILES) : p.nparts;
   // Kept pass: the fewest kept rows per work-group (32, 64, 128, ...) that
   // keep the launch within one resident round (VP_KEPT_WGS work-groups), so no
   // work-group waits for a second round (the 64 x 32k batch: 128 rows, 1792
@@ -99,8 +117,8 @@ Plan make_plan(const vp_shape& s) {
   // 1-sequence batch, 381.9 -> 351.9 at the 72B-class loop); beyond one round
   // the text pass is split over two (the 64 x 32k batch: 3081 -> 3663 us).
   p.text_kept_one_launch =
-      one_launch ? pairs * queries(s) * p.nsplit <= VP_KEPT_WGS / 2
-                 : (p.nparts + static_cast<int64_t>(queries(s)) * p.nsplit) * pairs <= VP_KEPT_WGS;
+      p.text_waves > 1 ? pairs * queries(s) * p.nsplit <= VP_KEPT_WGS / 2
+                       : (p.text_parts + static_cast<int64_t>(queries(s)) * p.nsplit) * pairs <= VP_KEPT_WGS;
   // A step whose kept pass would be a handful of work-groups folds the kept
   // rows into the merge (their K and V rows read there): bf16 caches, every
   // text part and kept row in one batch per head.
@@ -115,9 +133,10 @@ Plan make_plan(const vp_shape& s) {
   p.zs = off;
   off = align256(off + B * static_cast<size_t>(s.n_kv_heads) * p.zs_rows * static_cast<size_t>(p.zs_gp) * 4);
   p.stats = off;
-  off = align256(off + B * Hq * p.nparts * 8 * 4);
+  const size_t part_slots = std::max(p.nparts, p.text_parts);
+  off = align256(off + B * Hq * part_slots * 8 * 4);
   p.acc = off;
-  off = align256(off + B * Hq * p.nparts * d * 4);
+  off = align256(off + B * Hq * part_slots * d * 4);
   p.head = off;
   off = align256(off + B * Hq * 2 * 4);
   p.kstats = off;

@@ -1,0 +1,112 @@
+"""The sizes at which a kernel's work changes hands: cache lengths around the
+32-row tiles and the four-wave parts of the one-launch context pass, and rows of
+visual tokens around the key counts that a selecting thread holds in registers
+(2, 4, ..., 32 keys of 1024 threads; more stay in LDS or memory).
+
+Tolerances: real outputs against the fp64 reference as in _parity; the masses of
+the call without V against those with V to 4e-6 (a few fp32 ulps: separately
+compiled kernels); selections are exact."""
+import numpy as np
+import pytest
+import torch
+
+from _parity import assert_step_equals_calls, check_sequence, kept_in_merge, small_workload, tile_batch
+from oracle import plant as P
+from oracle import vp_oracle as O
+from paper_2605_31457_amd import step as S
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(tag, w, ref, n_ref, max_vis=None):
+    ds = S.DeviceStep(w) if max_vis is None else S.DeviceStep(w, max_vis=max_vis)
+    ds.decode_step()
+    g = ds.results()
+    ds.run(fused=True)
+    assert_step_equals_calls(g, ds.results(), True, kept_in_merge(ds), tag)
+    for b in range(w.B):
+        check_sequence(tag, w, g, b, ref[b % n_ref], b_src=b % n_ref)
+    return ds, g
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d", [("bf16", 28, 4, 128), ("bf16", 4, 1, 64), ("f32", 4, 2, 128), ("f32", 4, 1, 64)])
+def test_lengths_around_tiles_and_parts(dtype, Hq, Hkv, d):
+    """Waves of a part with no tile, one tile or an odd visual tile left over;
+    segments that begin and end on, before and after a tile's edge."""
+    lens = [1, 31, 32, 33, 64, 95, 128, 129, 160, 257, 1023, 1057]
+    segs = [[(0, 1)], [], [(0, 32)], [(31, 2)], [(0, 32)], [(1, 63)], [(32, 64)], [(0, 97)], [(31, 1), (33, 63)],
+            [(0, 256)], [(14, 500), (514, 31), (546, 400)], [(33, 1023)]]
+    w = small_workload(seed=71, B=len(lens), Hq=Hq, Hkv=Hkv, d=d, lens=lens, segs=segs, dtype=dtype, S_cap=1100)
+    ref, _ = P.plant(w, P.params_of(w))
+    ds, g = _check(f"edges {dtype} d={d}", w, ref, w.B)
+    ds.run(fused=False)  # no V in the mass call: statistics alone in the one launch
+    n = ds.results()
+    for key in ("mass_head", "mass_seq", "scores"):
+        np.testing.assert_allclose(n[key], g[key], rtol=4e-6, atol=1e-30, err_msg=key)
+    for key in ("k", "vis_idx"):
+        assert np.array_equal(n[key], g[key]), key
+
+
+@pytest.mark.parametrize("B,Hkv,d", [(64, 4, 64), (65, 4, 128), (128, 4, 64), (513, 1, 64)])
+def test_many_sequence_and_kv_head_pairs(B, Hkv, d):
+    """256 pairs and fewer share a resident round of four-wave parts; more take two
+    parts (one from 512 pairs), and single-wave ones in a later layer's text pass,
+    whose own text rows the call without the workspace's text part reads."""
+    base = small_workload(seed=76, B=3, Hq=4 * Hkv, Hkv=Hkv, d=d, lens=[290, 33, 150],
+                          segs=[[(20, 100), (130, 31)], [(1, 31)], []])
+    ref, _ = P.plant(base, P.params_of(base))
+    w = tile_batch(base, B)
+    ds, g = _check(f"{B} x {Hkv}", w, ref, 3)
+    ds.run(fused=False)
+    n = ds.results()
+    for b in range(w.B):
+        check_sequence(f"{B} x {Hkv} own text", w, n, b, ref[b % 3], b_src=b % 3)
+
+
+@pytest.mark.parametrize("n_vis", [2047, 2048, 2049, 4097, 8192, 8193, 16385, 32768, 32769])
+def test_step_selection_around_the_keys_a_thread_holds(n_vis):
+    w = small_workload(seed=72, B=2, Hq=4, Hkv=1, d=64, lens=[n_vis + 60, 200], segs=[[(30, n_vis)], [(20, 150)]])
+    ref, _ = P.plant(w, P.params_of(w))
+    _check(f"{n_vis} visual tokens", w, ref, w.B)
+
+
+@pytest.mark.parametrize("n_vis", [1000, 2049, 9000, 20000])
+def test_step_selection_with_one_work_group_per_row(n_vis):
+    """256 rows: each row's keys go from LDS to registers in one work-group."""
+    base = small_workload(seed=73, B=2, Hq=4, Hkv=1, d=64, lens=[n_vis + 60, 200], segs=[[(30, n_vis)], [(20, 150)]])
+    ref, _ = P.plant(base, P.params_of(base))
+    _check(f"256 rows of {n_vis}", tile_batch(base, 256), ref, 2, max_vis=n_vis)
+
+
+@pytest.mark.parametrize("n", [1, 63, 2047, 2048, 2049, 4096, 4097, 8193, 16384, 16385, 32768, 32769])
+def test_topk_around_the_keys_a_thread_holds(n):
+    """Distinct, tied, equal and special scores; k from 0 over the count that fits
+    the staged ranks to every token. The second row is shorter than the first."""
+    rng = np.random.default_rng(74)
+    n1 = max(1, n - 65)
+    segs = [[(5, n)], [(5, n1)]]
+    lens = [n + 10, n1 + 10]
+    w = small_workload(seed=75, B=2, Hq=1, Hkv=1, d=64, lens=lens, segs=segs, spike=0)
+    ds = S.DeviceStep(w, k_cap=n, max_vis=n)
+    vis = [O.visual_positions(lens[b], segs[b]) for b in range(2)]
+    for kind in ("distinct", "tied", "equal", "extreme"):
+        sc = rng.random((2, n)).astype(np.float32)
+        if kind == "tied":
+            sc = (np.floor(sc * 16) / 16).astype(np.float32)
+        elif kind == "equal":
+            sc[:] = np.float32(1.0 / 7.0)
+        elif kind == "extreme":  # zeros, the least and largest floats and +inf among the scores
+            sc[:, ::3] = 0.0
+            sc[:, 1::7] = np.float32(np.finfo(np.float32).tiny)
+            sc[:, 2::11] = np.float32(np.finfo(np.float32).max)
+            sc[:, 4::301] = np.inf
+        for k in sorted({0, 1, n // 20, n // 2, n - 1, n}):
+            ds.scores.copy_(torch.from_numpy(sc))
+            ds.k.copy_(torch.tensor([k, k], dtype=torch.int32))
+            ds.select_topk()
+            got = ds.vis_idx.cpu().numpy()
+            for b, nb in enumerate((n, n1)):
+                kb = min(k, nb)
+                want = O.select_top_k(sc[b, :nb].astype(np.float64), vis[b], kb)
+                assert np.array_equal(got[b, :kb], want), (kind, k, b)
+                assert np.all(got[b, kb:] == -1), (kind, k, b)
