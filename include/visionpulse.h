@@ -340,6 +340,9 @@ vp_status vp_decode_step_static(const vp_shape* shape, const vp_layout* layout, 
  *                               pass); vp_sparse_decode_attn without that flag
  *                               keeps its kept pass, so its output then agrees
  *                               with theirs to rounding, not bit for bit.
+ * (The same holds, without a flag, where batch * n_kv_heads exceeds 256 in
+ * one context launch: a layer's own text pass has other
+ * parts there.)
  */
 #define VP_PLAN_ONE_CONTEXT_LAUNCH 1
 #define VP_PLAN_FUSED_TAIL 2
