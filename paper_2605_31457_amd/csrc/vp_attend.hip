@@ -369,23 +369,27 @@ struct Pass {
       // the first tile's come in as kp_loaded, requested before the budget)
       const int t = t0 + lane;
       n.kp = (lane < 32 && t < r1) ? (kp_loaded != -2 ? kp_loaded : kept[t]) : -1;
+      if constexpr (PAGED) {
+        if (lane < 32) n.blk = block_of((n.kp < 0 || n.kp >= L) ? 0 : n.kp);
+      }
     } else {
       if (t0 < r1) {
         n.w.seek(t0);
         n.cls = classify(n.w, t0, min(t0 + 32, r1));
-      }
-    }
-    if constexpr (PAGED) {
-      // the physical block of each of the tile's rows (the row that row_pos
-      // will read: clipped positions included)
-      if (lane < 32) {
-        int p;
-        if constexpr (KEPT) p = (n.kp < 0 || n.kp >= L) ? 0 : n.kp;
-        else p = min(t0 + lane, L - 1);
-        n.blk = bt[p >> __builtin_ctz(static_cast<unsigned>(bmask + 1))];
+        if constexpr (PAGED) {
+          if (lane < 32) n.blk = block_of(min(t0 + lane, L - 1));
+        }
       }
     }
     return n;
+  }
+
+  // paged caches: the physical block of position p (of each of a tile's rows: the
+  // position that row_pos will read, clipped ones included). Only called where the
+  // tile has rows, so 0 <= p < L: waves without tiles, and every wave of an empty
+  // sequence, read no entry of the block table
+  __device__ __forceinline__ int block_of(int p) const {
+    return bt[p >> __builtin_ctz(static_cast<unsigned>(bmask + 1))];
   }
 
   // kept pass from the spill: the logits of this lane's 8 rows (head n16 of

@@ -139,3 +139,48 @@ def test_paged_two_launch_plan():
         flat.run(fused=fused)
         _same(flat.results(), paged.results(), f"two-launch P=32 calls fused={fused}")
     _log(f"paged two-launch: k={[ref[b].k for b in range(4)]}...")
+
+
+EMPTY = {
+    # kept rows in the merge launch; a kept pass (fp32); four-wave parts of several tiles
+    "bf16-d128": (dict(seed=81, B=3, Hq=8, Hkv=2, d=128, lens=[70, 120, 90], segs=[[(5, 40)], [(10, 60)], [(0, 40)]]), 16),
+    "f32-d64": (dict(seed=82, dtype="f32", B=3, Hq=4, Hkv=1, d=64, lens=[70, 120, 90],
+                     segs=[[(5, 40)], [(10, 60)], [(0, 40)]]), 32),
+    "f32-d128": (dict(seed=83, dtype="f32", B=3, Hq=4, Hkv=1, d=128, lens=[70, 400, 90],
+                      segs=[[(5, 40)], [(10, 300)], [(0, 40)]]), 64),
+    "bf16-d64-long": (dict(seed=84, B=3, Hq=16, Hkv=4, d=64, lens=[700, 1500, 900],
+                           segs=[[(5, 400)], [(10, 1100)], [(0, 64), (100, 700)]]), 32),
+}
+
+
+@pytest.mark.parametrize("first", [True, False])
+@pytest.mark.parametrize("name", sorted(EMPTY))
+def test_paged_zero_length_sequence(name, first):
+    """A sequence of length 0 (the first of the batch, whose table row has nothing
+    before it, or the last) uses no block: the step, the four calls and a layer that
+    reads its own text rows give the empty context's results for it and, for its
+    neighbours, the bits of the contiguous caches."""
+    spec, bs = EMPTY[name]
+    w = small_workload(**spec)
+    e = 0 if first else w.B - 1
+    ref, _ = P.plant(w, P.params_of(w))
+    flat = S.DeviceStep(w)
+    paged = S.DeviceStep(w, block_size=bs, block_seed=9)
+    for ds in (flat, paged):
+        ds.seq_len[e] = 0
+    for run in (lambda ds: ds.decode_step(), lambda ds: ds.run(fused=True), lambda ds: ds.run(fused=False)):
+        got = []
+        for ds in (flat, paged):
+            ds.scores.fill_(-1.0)
+            ds.out.fill_(7.0)
+            run(ds)
+            got.append(ds.results())
+        _same(got[0], got[1], f"{name} with an empty sequence")
+        g = got[1]
+        for b in range(w.B):
+            if b != e:
+                check_sequence(f"{name} beside an empty sequence", w, g, b, ref[b])
+        assert np.all(g["mass_head"][e] == 0.0) and np.all(g["mass_seq"][e] == 0.0)
+        assert int(g["k"][e]) == 0 and np.all(g["vis_idx"][e] == -1)
+        assert np.all(g["scores"][e] == -1.0), "no visual rank: no score is written"
+        assert np.all(g["out"][e] == 0.0)
