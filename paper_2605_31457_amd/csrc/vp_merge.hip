@@ -103,9 +103,17 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const MergeArgs a)
 #pragma unroll 4
     for (int i = r; i < np; i += R) {
       const float2 v = ml(i);
-      const float w = v.y > 0.f ? fast_exp2(v.x - M) : 0.f;
-      const float4 x = i < nc ? ac[static_cast<size_t>(i) * COLS] : ka[static_cast<size_t>(i - nc) * COLS];
-      den += w * v.y;
+      float4 x = i < nc ? ac[static_cast<size_t>(i) * COLS] : ka[static_cast<size_t>(i - nc) * COLS];
+      // an empty partial's value row was never written (any bits, NaN among them):
+      // it is taken as zeros, not multiplied by zero (selects: a branch would
+      // let the compiler wait for each load)
+      const bool any = v.y > 0.f;
+      const float w = any ? fast_exp2(v.x - M) : 0.f;
+      x.x = any ? x.x : 0.f;
+      x.y = any ? x.y : 0.f;
+      x.z = any ? x.z : 0.f;
+      x.w = any ? x.w : 0.f;
+      den += any ? w * v.y : 0.f;
       num.x += w * x.x;
       num.y += w * x.y;
       num.z += w * x.z;
