@@ -285,6 +285,11 @@ __device__ __forceinline__ void store_acc(float* dst, const f32x4 (&acc)[N], int
   }
 }
 
+// What a tile's logits are taken relative to: the running maximum, or zero while
+// no row but ones of logit -inf was seen (their weights are then 2^-inf = 0;
+// relative to the maximum of -inf they would be NaN)
+__device__ __forceinline__ float finite_or_zero(float m) { return m == kNegInf ? 0.f : m; }
+
 enum TileClass : int { TILE_TEXT = 0, TILE_VIS = 1, TILE_MIXED = 2 };
 
 // class of tile [t0, t_end) given a walker already seeked to t0
@@ -545,10 +550,11 @@ struct Pass {
         Lm_v *= up ? fast_exp2((m_v - lmax) * a.inv_tau_m) : 1.f;
         m_v = up ? lmax : m_v;
       }
+      const float ref = finite_or_zero(m_v);
       float ts = 0.f, tm = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float d = FULL || (vis & (1u << i)) ? z[i] - m_v : kNegInf;
+        const float d = FULL || (vis & (1u << i)) ? z[i] - ref : kNegInf;
         ts += fast_exp2(d * a.inv_tau_s);
         tm += fast_exp2(d * a.inv_tau_m);
       }
@@ -601,11 +607,12 @@ struct Pass {
         }
         m_t = up ? tm : m_t;
       }
+      const float ref = finite_or_zero(m_t);
       float p[8];
       float ps = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        p[i] = (att & (1u << i)) ? fast_exp2(z[i] - m_t) : 0.f;
+        p[i] = (att & (1u << i)) ? fast_exp2(z[i] - ref) : 0.f;
         ps += p[i];
       }
       l_t += ps;
@@ -613,7 +620,7 @@ struct Pass {
         float tm = 0.f, ts = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const float d = (att & (1u << i)) ? z[i] - m_t : kNegInf;
+          const float d = (att & (1u << i)) ? z[i] - ref : kNegInf;
           tm += fast_exp2(d * a.inv_tau_m);
           if (!a.tau_s_one) ts += fast_exp2(d * a.inv_tau_s);
         }
@@ -680,17 +687,20 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
     store_acc<DT, D, C::ACC_N>(reinterpret_cast<float*>(lds + wave * PassLds<DT, D, MODE, W>::BYTES) + s.n16 * PITCH,
                                s.acc, s.a4);
   __syncthreads();
-  // weight of wave w's sums after the rescaling of column c (a maximum) of head h by 1/tau
+  // the common maximum of column c of head h
   auto top = [&](int h, int c) {
     float M = kNegInf;
 #pragma unroll
     for (int w = 0; w < W; ++w) M = fmaxf(M, ws.v[w][h][c]);
     return M;
   };
+  // the weight of wave w's sums after its maximum (column c) is raised to M, at 1/tau
   auto weight = [&](int w, int h, int c, float M, float inv_tau) {
     const float m = ws.v[w][h][c];
     return m == kNegInf ? 0.f : fast_exp2((m - M) * inv_tau);
   };
+  // does wave w have attention weights for head h (the merge's rule for partials)
+  auto attends = [&](int w, int h) { return ws.v[w][h][4] > 0.f; };
   const size_t head0 = static_cast<size_t>(b) * a.T * a.Hq + static_cast<size_t>(g) * a.T * a.G;
   if (s.a4 == 0 && s.hv) {
     const int h = s.n16;
@@ -710,7 +720,7 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
       double l = 0.0, lm = 0.0, ls = 0.0;
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        l += static_cast<double>(weight(w, h, 3, M, 1.f)) * ws.v[w][h][4];
+        l += attends(w, h) ? static_cast<double>(weight(w, h, 3, M, 1.f)) * ws.v[w][h][4] : 0.0;
         if constexpr (P::TSTATS) {
           lm += static_cast<double>(weight(w, h, 3, M, a.inv_tau_m)) * ws.v[w][h][5];
           ls += static_cast<double>(weight(w, h, 3, M, a.inv_tau_s)) * ws.v[w][h][6];
@@ -731,13 +741,14 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
       float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int w = 0; w < W; ++w) {
+        const bool on = attends(w, h);
         const float f = weight(w, h, 3, M, 1.f);
         const float4 x = reinterpret_cast<const float4*>(
             reinterpret_cast<const float*>(lds + w * PassLds<DT, D, MODE, W>::BYTES) + h * PITCH)[c];
-        t.x = fmaf(f, x.x, t.x);
-        t.y = fmaf(f, x.y, t.y);
-        t.z = fmaf(f, x.z, t.z);
-        t.w = fmaf(f, x.w, t.w);
+        t.x = on ? fmaf(f, x.x, t.x) : t.x;
+        t.y = on ? fmaf(f, x.y, t.y) : t.y;
+        t.z = on ? fmaf(f, x.z, t.z) : t.z;
+        t.w = on ? fmaf(f, x.w, t.w) : t.w;
       }
       reinterpret_cast<float4*>(a.acc + ((head0 + h) * a.nparts + part) * D)[c] = t;
     }
