@@ -157,9 +157,10 @@ EMPTY = {
 @pytest.mark.parametrize("name", sorted(EMPTY))
 def test_paged_zero_length_sequence(name, first):
     """A sequence of length 0 (the first of the batch, whose table row has nothing
-    before it, or the last) uses no block: the step, the four calls and a layer that
-    reads its own text rows give the empty context's results for it and, for its
-    neighbours, the bits of the contiguous caches."""
+    before it, or the last) uses no block, so its table entries name none (-1): the
+    step, the four calls and a layer that reads its own text rows give the empty
+    context's results for it and, for its neighbours, the bits of the contiguous
+    caches."""
     spec, bs = EMPTY[name]
     w = small_workload(**spec)
     e = 0 if first else w.B - 1
@@ -168,6 +169,7 @@ def test_paged_zero_length_sequence(name, first):
     paged = S.DeviceStep(w, block_size=bs, block_seed=9)
     for ds in (flat, paged):
         ds.seq_len[e] = 0
+    paged.block_table[e] = -1
     for run in (lambda ds: ds.decode_step(), lambda ds: ds.run(fused=True), lambda ds: ds.run(fused=False)):
         got = []
         for ds in (flat, paged):
