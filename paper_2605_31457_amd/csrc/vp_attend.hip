@@ -699,8 +699,6 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
     const float m = ws.v[w][h][c];
     return m == kNegInf ? 0.f : fast_exp2((m - M) * inv_tau);
   };
-  // does wave w have attention weights for head h (the merge's rule for partials)
-  auto attends = [&](int w, int h) { return ws.v[w][h][4] > 0.f; };
   const size_t head0 = static_cast<size_t>(b) * a.T * a.Hq + static_cast<size_t>(g) * a.T * a.G;
   if (s.a4 == 0 && s.hv) {
     const int h = s.n16;
@@ -720,7 +718,7 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
       double l = 0.0, lm = 0.0, ls = 0.0;
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        l += attends(w, h) ? static_cast<double>(weight(w, h, 3, M, 1.f)) * ws.v[w][h][4] : 0.0;
+        l += static_cast<double>(weight(w, h, 3, M, 1.f)) * ws.v[w][h][4];
         if constexpr (P::TSTATS) {
           lm += static_cast<double>(weight(w, h, 3, M, a.inv_tau_m)) * ws.v[w][h][5];
           ls += static_cast<double>(weight(w, h, 3, M, a.inv_tau_s)) * ws.v[w][h][6];
@@ -741,14 +739,13 @@ __device__ __forceinline__ void combine_waves(const AttendArgs& a, Pass<DT, D, M
       float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        const bool on = attends(w, h);
         const float f = weight(w, h, 3, M, 1.f);
         const float4 x = reinterpret_cast<const float4*>(
             reinterpret_cast<const float*>(lds + w * PassLds<DT, D, MODE, W>::BYTES) + h * PITCH)[c];
-        t.x = on ? fmaf(f, x.x, t.x) : t.x;
-        t.y = on ? fmaf(f, x.y, t.y) : t.y;
-        t.z = on ? fmaf(f, x.z, t.z) : t.z;
-        t.w = on ? fmaf(f, x.w, t.w) : t.w;
+        t.x = fmaf(f, x.x, t.x);
+        t.y = fmaf(f, x.y, t.y);
+        t.z = fmaf(f, x.z, t.z);
+        t.w = fmaf(f, x.w, t.w);
       }
       reinterpret_cast<float4*>(a.acc + ((head0 + h) * a.nparts + part) * D)[c] = t;
     }

@@ -183,7 +183,7 @@ __device__ __forceinline__ float4 bf16x4_to_f32(uint2 u) {
 // fill the text pass's tail).
 // Every kept slot up to k_cap is requested with the budget, the length and the
 // text partials; entries past the budget and positions outside [0, L) are skipped.
-template <int D>
+template <int D, bool PAGED>
 __global__ __launch_bounds__(kMergeThreads) void merge_kept_kernel(const MergeArgs a) {
   constexpr int COLS = D / 4;
   constexpr int R = kMergeThreads / COLS;
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kept_kernel(const MergeAr
     const int i = r + j * R;
     pos[j] = i < a.k_cap ? kl[i] : -1;
   }
-  if (a.block_table && L == 0) {
+  if (PAGED && L == 0) {
     // an empty sequence uses no block: nothing is read through its table, whose
     // entries may hold anything
     if (r == 0) reinterpret_cast<uint2*>(static_cast<uint16_t*>(a.out) + ob * D)[col] = make_uint2(0u, 0u);
@@ -242,7 +242,7 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kept_kernel(const MergeAr
   for (int j = 0; j < kKeptHeld; ++j) {
     okk[j] = r + j * R < kb && pos[j] >= 0 && pos[j] < L;
     const int p = okk[j] ? pos[j] : 0;
-    if (a.block_table) {
+    if constexpr (PAGED) {
       const int blk = a.block_table[static_cast<size_t>(b) * a.nblk + (p >> a.bs_log2)];
       off[j] = static_cast<size_t>(blk) * a.sb + static_cast<size_t>(g) * a.sh +
                static_cast<size_t>(p & ((1 << a.bs_log2) - 1)) * a.ss;
@@ -328,10 +328,15 @@ int merge_kept_max_rows(int head_dim) { return kKeptHeld * (kMergeThreads / (hea
 
 hipError_t launch_merge_kept(const MergeArgs& a, int head_dim, hipStream_t st) {
   const dim3 grid(a.T * a.Hq, a.B);
-  if (head_dim == 128)
-    hipLaunchKernelGGL(merge_kept_kernel<128>, grid, dim3(kMergeThreads), 0, st, a);
+  const bool paged = a.block_table != nullptr;
+  if (head_dim == 128 && paged)
+    hipLaunchKernelGGL((merge_kept_kernel<128, true>), grid, dim3(kMergeThreads), 0, st, a);
+  else if (head_dim == 128)
+    hipLaunchKernelGGL((merge_kept_kernel<128, false>), grid, dim3(kMergeThreads), 0, st, a);
+  else if (head_dim == 64 && paged)
+    hipLaunchKernelGGL((merge_kept_kernel<64, true>), grid, dim3(kMergeThreads), 0, st, a);
   else if (head_dim == 64)
-    hipLaunchKernelGGL(merge_kept_kernel<64>, grid, dim3(kMergeThreads), 0, st, a);
+    hipLaunchKernelGGL((merge_kept_kernel<64, false>), grid, dim3(kMergeThreads), 0, st, a);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
