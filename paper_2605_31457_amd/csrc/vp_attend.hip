@@ -469,6 +469,14 @@ struct Pass {
                                        kCopyPolicy);
   }
 
+  // Whole tiles have code without masks of their own, and masked tiles compute
+  // their addresses anew (unhoist_lane): the bf16 passes, whose registers must
+  // leave room for two waves per SIMD. An fp32 wave has a SIMD's registers to
+  // itself: there two copies of the tile's code and addresses computed per tile
+  // cost 8 to 22% of the step (16 x 28/4 heads x 7k tokens 112.8 -> 104.0 us without them,
+  // 3 x 16 heads of 64 x 2k 40.5 -> 33.7).
+  static constexpr bool WHOLE = C::BF && !KEPT;
+
   // Lane indices that the compiler cannot prove unchanged from tile to tile:
   // what the rare tiles compute from them is computed there, instead of being
   // kept in registers through the loop.
@@ -917,7 +925,7 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
         if (s.needs_v(t0)) s.copy_even_rows(s.Vb + off, dma + C::SUB_ROWS_BYTES);
       } else {
         size_t off[C::COPIES];
-        if constexpr (!P::KEPT) s.unhoist_lane();
+        if constexpr (P::WHOLE) s.unhoist_lane();
         s.row_offsets(t0, off);
         if constexpr (!P::ZSPILL) s.copy_rows(s.Kb, off, dma);
         if (s.needs_v(t0)) s.copy_rows(s.Vb, off, dma + C::SUB_ROWS_BYTES);
@@ -927,7 +935,7 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
           s.copy_even_rows(s.Kb + s.tile_offset(t1), dma + C::SUB_ROWS_BYTES);
         } else {
           size_t off[C::COPIES];
-          s.unhoist_lane();
+          if constexpr (P::WHOLE) s.unhoist_lane();
           s.row_offsets(t1, off);
           s.copy_rows(s.Kb, off, dma + C::SUB_ROWS_BYTES);
         }
@@ -949,10 +957,10 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
     Sub t = t0;
 #pragma unroll 1
     for (int i = 0;; ++i) {
-      if (!P::KEPT && t.cls != TILE_MIXED && t.t0 + 32 <= min(s.L, s.L0)) {
-        s.template process<true>(t, kblk, vblk, stage, zk);
+      if (P::WHOLE && t.cls != TILE_MIXED && t.t0 + 32 <= min(s.L, s.L0)) {
+        s.template process<P::WHOLE>(t, kblk, vblk, stage, zk);
       } else {
-        if constexpr (!P::KEPT) s.unhoist_lane();
+        if constexpr (P::WHOLE) s.unhoist_lane();
         s.template process<false>(t, kblk, vblk, stage, zk);
       }
       if (!PAIRS || !pair || i == 1) break;
