@@ -1037,6 +1037,7 @@ __global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(attend_w
 attend_waves_kernel(const AttendArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[W * PassLds<DT, D, MODE, W>::BYTES];
   __shared__ WaveStats<W> ws;
+  static_assert((sizeof(lds) + sizeof(ws)) * (resident_groups(DT, D) / 256) <= 160 * 1024, "work-groups of a CU");
   const int wave = wave_index();
   if (static_cast<int>(blockIdx.x) == a.nparts) {
     if (wave == 0 && blockIdx.y == 0) step_setup<D>(a, blockIdx.z);
@@ -1112,7 +1113,7 @@ template <int DT, int D, int PG>
 hipError_t launch_waves(const AttendArgs& a, int mode, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
   constexpr int W = kPartWaves;
   int gx = a.nparts;
-  if ((mode & MODE_VIS) != 0 && static_cast<int64_t>(a.nparts + 1) * a.Hkv * a.B * W <= kResidentWaves)
+  if ((mode & MODE_VIS) != 0 && static_cast<int64_t>(a.nparts + 1) * a.Hkv * a.B <= resident_groups(DT, D))
     gx = a.nparts + 1;  // room for the step setup's own work-groups
   else if (mode == MODE_TEXT_KEPT) gx = a.nparts + (a.T * a.nsplit + W - 1) / W;
   const dim3 grid(gx, a.Hkv, a.B);

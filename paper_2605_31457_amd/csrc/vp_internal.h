@@ -38,8 +38,10 @@ __host__ __device__ inline int vis_len(int L, int T) { return L - T + 1 > 0 ? L 
 #endif
 constexpr int kPartWaves = VP_PART_WAVES;
 
-// One resident round of the passes that read V: 8 waves per CU x 256 CUs
-constexpr int kResidentWaves = 2048;
+// Four-wave work-groups of the one launch that the GPU (256 CUs) holds at a time:
+// two per CU (8 waves, what their registers allow); one where their LDS allows no
+// more (fp32 rows of 128: 4 x 34 KB of a CU's 160)
+constexpr int resident_groups(int dtype, int head_dim) { return 256 * (dtype == VP_F32 && head_dim == 128 ? 1 : 2); }
 
 // Work decomposition and workspace carving, a pure function of the shape.
 struct Plan {
@@ -50,7 +52,7 @@ struct Plan {
   int nsplit;   // ceil(k_cap / split)
   int text_parts;  // parts and waves of the text pass that a later layer runs for itself
   int text_waves;
-  bool text_kept_one_launch;  // a later layer's text and kept passes fit one resident round together
+  bool text_kept_one_launch;  // a later layer's text and kept passes share a launch
   bool merge_kept;            // the step folds the kept rows into the merge (no kept pass)
   int zs_rows;    // rows per spill plane: max_seq_len rounded up to 32
   int zs_gp;      // floats per spill row: the query group padded to 8 or 16

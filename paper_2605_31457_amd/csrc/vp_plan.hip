@@ -22,9 +22,6 @@ int rows_per_seq(const vp_shape& s) { return queries(s) * rows_per_query(s); }
 // four waves, where one wave per part and role left the select and merge
 // launches 256 partials per head to read at one 30k-token sequence (per pass
 // 61.8 -> 49.2 us there, 80.5 -> 76.5 at the ragged 16-sequence batch).
-#ifndef VP_ONE_LAUNCH_WAVES
-#define VP_ONE_LAUNCH_WAVES 2048
-#endif
 #ifndef VP_ONE_LAUNCH_TILES
 #define VP_ONE_LAUNCH_TILES 1  // 32-row tiles per wave of the one launch, at least
 #endif
@@ -82,14 +79,23 @@ Plan make_plan(const vp_shape& s) {
   auto capped = [&](int64_t n, int64_t least) {
     return static_cast<int>(std::max<int64_t>(1, std::min(n, (tiles + least - 1) / least)));
   };
-  // rounded down (a second round of 72 to 192 (sequence, KV head) pairs measured
-  // 1.09 to 1.12 times the step), except that one part per pair would leave up to
-  // half of the GPU idle: two parts there (264 pairs of 3.7k tokens 125.2 -> 121.7
-  // us per step, 288 of head_dim 64 72.5 -> 65.2, 504 104.4 -> 102.7; 384 105.6 -> 108.6)
-  constexpr int64_t kRound = VP_ONE_LAUNCH_WAVES / kPartWaves;
-  const bool many_pairs = one_launch && pairs > kRound / 2;
+  // A round is what is resident at a time. Rounded down: a second round costs more
+  // than the finer parts give (two rounds instead of one of fp32 rows of 128: 4 x 29k tokens 53.5
+  // -> 61.8 us per step, 48 pairs of 745 36.4 -> 42.0, 96 of 2k 61 -> 73; bf16 72 to 192 pairs
+  // 1.09 to 1.12 times), except where one part per pair leaves a good part of the round or of
+  // the second one idle: two parts there.
+  //   half a round to one (bf16): one and two parts 125.2 and 121.4 us at 264 pairs, 93.4 and 89.7 at
+  //   288, 104.4 and 103.0 at 504, but 105.8 and 109.0 at 384 (fp32 rows of 128: 98 and 108 at 160 pairs);
+  //   one round to one and a half: 113.4 and 107.9 at 640 pairs, 110.4 and 103.7 at 768
+  //   (fp32 rows of 128: 162.5 and 146.4 at 272 pairs, 191 and 179 at 384; beyond: 137 and 151 at 416)
+  const int64_t round = resident_groups(s.dtype, s.head_dim);
+  const bool single_group = round == 256;  // one work-group per CU
+  const bool two_parts =
+      pairs > round ? 2 * pairs <= 3 * round
+                    : !single_group && 2 * pairs > round && pairs < round && (4 * pairs < 3 * round || 8 * pairs >= 7 * round);
+  const bool many_pairs = one_launch && pairs > 256;
   p.nparts = !one_launch ? capped((VP_TWO_LAUNCH_PARTS + pairs - 1) / pairs, min_tiles)
-                         : capped(many_pairs && pairs < kRound ? 2 : kRound / pairs, min_tiles);
+                         : capped(two_parts ? 2 : round / pairs, min_tiles);
   // A later layer's text pass has the context pass's parts, but with many pairs
   // single-wave parts, one to four per pair: they balance the text rows alone
   // better (a later layer with four-wave parts and here: 68.1 and 64.8 us at 264
@@ -111,8 +117,24 @@ Plan make_plan(const vp_shape& s) {
   }
 #endif
   p.nsplit = (s.k_cap + p.split - 1) / p.split;
+  // A later layer's kept work-groups share the launch of its text parts. Where a CU
+  // holds one work-group they would wait for a whole CU to fall free: the parts
+  // (the step's too, so that both give the same bits) are fewer by what they need,
+  // if that is at most a quarter and no wave's chain of tiles gets longer (a later
+  // layer of 4 x 3.3k tokens, 28/4 heads: 23.4 -> 17.5 us, 6 x 745, 32/8 heads: 19.6 -> 17.1; the steps
+  // within 0.3 us). With two per CU the steps lose as much as the later layers
+  // gain (2 x 3.6k tokens, 32/32 heads: 38.9 -> 40.5 and 23.6 -> 23.2 us).
+  if (one_launch && single_group && !many_pairs) {
+    const int64_t kept = (static_cast<int64_t>(queries(s)) * p.nsplit + kPartWaves - 1) / kPartWaves;
+    const int64_t room = round / pairs - kept;
+    auto chain = [&](int64_t parts) { return (tiles + kPartWaves * parts - 1) / (kPartWaves * parts); };
+    if (p.nparts > room && 4 * room >= 3 * p.nparts && chain(room) == chain(p.nparts))
+      p.nparts = p.text_parts = static_cast<int>(room);
+  }
   // A later layer (its own text rows, the anchor's kept list) launches its text
-  // and kept passes together when both fit one resident round: the kept
+  // and kept passes together: with four-wave text parts, which fill a round by
+  // themselves, when the kept splits are at most half a round of waves (text waves not
+  // counted); with single-wave ones when both fit one resident round. The kept
   // work-groups then fill the text pass's tail (8 layers: 131.8 -> 98.6 us at the
   // 1-sequence batch, 381.9 -> 351.9 at the 72B-class loop); beyond one round
   // the text pass is split over two (the 64 x 32k batch: 3081 -> 3663 us).

@@ -110,3 +110,31 @@ def test_topk_around_the_keys_a_thread_holds(n):
                 want = O.select_top_k(sc[b, :nb].astype(np.float64), vis[b], kb)
                 assert np.array_equal(got[b, :kb], want), (kind, k, b)
                 assert np.all(got[b, kb:] == -1), (kind, k, b)
+
+
+def _step_calls_and_own_text(tag, w, ref, n_ref):
+    """The step against the reference and the calls, and the layer that reads its own
+    text rows: the step's bits, except where the header says to rounding only."""
+    ds, g = _check(tag, w, ref, n_ref)
+    ds.run(fused=False)
+    n = ds.results()
+    own_parts = w.B * w.Hkv > 256
+    assert_step_equals_calls(g, n, False, kept_in_merge(ds) or own_parts, tag)
+    for b in range(w.B):
+        check_sequence(f"{tag}, own text", w, n, b, ref[b % n_ref], b_src=b % n_ref)
+
+
+@pytest.mark.parametrize("dtype,Hkv,d,B,L", [
+    # fp32 rows of 128 (one four-wave work-group per CU): parts of one round, fewer
+    # where the kept work-groups need slots, one per pair, two past a round, one again
+    ("f32", 2, 128, 2, 2900), ("f32", 4, 128, 4, 3300), ("f32", 8, 128, 6, 745), ("f32", 4, 128, 40, 290),
+    ("f32", 4, 128, 64, 290), ("f32", 4, 128, 65, 290), ("f32", 4, 128, 96, 290), ("f32", 4, 128, 97, 290),
+    # bf16: two parts above half a round, one from three quarters, two from seven
+    # eighths, one at a round, two up to one and a half, one beyond
+    ("bf16", 4, 64, 95, 290), ("bf16", 4, 64, 96, 290), ("bf16", 4, 64, 111, 290), ("bf16", 4, 64, 112, 290),
+    ("bf16", 4, 64, 128, 290), ("bf16", 4, 64, 129, 290), ("bf16", 4, 64, 192, 290), ("bf16", 4, 64, 193, 290)])
+def test_parts_per_pair(dtype, Hkv, d, B, L):
+    base = small_workload(seed=77, B=3, Hq=2 * Hkv, Hkv=Hkv, d=d, lens=[L, 33, 150], dtype=dtype,
+                          segs=[[(20, L // 3), (L // 2, L // 9)], [(1, 31)], []])
+    ref, _ = P.plant(base, P.params_of(base))
+    _step_calls_and_own_text(f"{dtype} {B} x {Hkv} x {L}", tile_batch(base, B), ref, 3)
