@@ -1060,16 +1060,35 @@ attend_text_kept_kernel(const AttendArgs a) {
   static_assert(PassLds<DT, D, TEXT, W>::BYTES == PassLds<DT, D, KEPT, W>::BYTES, "LDS blocks of the waves");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[W * PassLds<DT, D, TEXT, W>::BYTES];
   __shared__ WaveStats<W> ws;
-  const int x = blockIdx.x;
   const int wave = wave_index();
+  int x = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+  const unsigned pairs = gridDim.y * gridDim.z;
+  const unsigned kept_groups = gridDim.x - a.nparts;  // of a pair
+  if (W > 1 && 16 * kept_groups * pairs > resident_groups(DT, D)) {
+    // the text work-groups of every pair come first: they fill the launch's first
+    // round by themselves, and the short kept ones follow as slots fall free. With
+    // the two interleaved, the last pairs' text work-groups waited for that round
+    // (a later layer at 72 (sequence, KV head) pairs x 10k tokens 53.5 -> 44.5 us,
+    // 80 x 9k 52.7 -> 43.5, 256 x 4k 64.4 -> 55.5; kept ones first: 47.3, 44.9, 59.5).
+    // With few kept work-groups that wait is short, and theirs at the end is not:
+    // interleaved (8 pairs x 8k tokens 14.4 us, text first 15.7; 16 x 9k 18.5 and 19.6)
+    const unsigned n = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+    const unsigned n_text = a.nparts * pairs;
+    const unsigned x0 = n < n_text ? 0 : a.nparts;
+    const unsigned per_pair = n < n_text ? a.nparts : kept_groups;
+    const unsigned i = n < n_text ? n : n - n_text;
+    const unsigned pair = i / per_pair;
+    x = static_cast<int>(x0 + i - pair * per_pair);
+    b = static_cast<int>(pair / gridDim.y);
+    g = static_cast<int>(pair - b * gridDim.y);
+  }
   if (x < a.nparts) {
-    attend_body<DT, D, TEXT, W>(a, lds, x, blockIdx.y, blockIdx.z, wave, &ws);
+    attend_body<DT, D, TEXT, W>(a, lds, x, g, b, wave, &ws);
   } else {
     const int j = (x - a.nparts) * W + wave;
     const int t = j / a.nsplit;
     if (t < a.T)
-      attend_body<DT, D, KEPT>(a, lds + wave * PassLds<DT, D, KEPT, W>::BYTES, j - t * a.nsplit, blockIdx.y * a.T + t,
-                               blockIdx.z);
+      attend_body<DT, D, KEPT>(a, lds + wave * PassLds<DT, D, KEPT, W>::BYTES, j - t * a.nsplit, g * a.T + t, b);
   }
 }
 

@@ -138,3 +138,26 @@ def test_parts_per_pair(dtype, Hkv, d, B, L):
                           segs=[[(20, L // 3), (L // 2, L // 9)], [(1, 31)], []])
     ref, _ = P.plant(base, P.params_of(base))
     _step_calls_and_own_text(f"{dtype} {B} x {Hkv} x {L}", tile_batch(base, B), ref, 3)
+
+
+@pytest.mark.parametrize("dtype,Hq,B,T", [("bf16", 8, 1, 1), ("bf16", 8, 8, 1), ("bf16", 8, 9, 1), ("bf16", 14, 5, 2),
+                                          ("bf16", 14, 6, 2), ("f32", 4, 4, 1), ("f32", 4, 5, 1)])
+def test_later_layer_work_group_order(dtype, Hq, B, T):
+    """Text and kept work-groups in one launch: interleaved while the kept ones (here
+    two per pair and query, rounded up) are at most a sixteenth of a round, all of the
+    text ones first beyond."""
+    base = small_workload(seed=78, B=3, Hq=Hq, Hkv=2, d=128, lens=[1300, 700, 40], dtype=dtype,
+                          segs=[[(20, 900), (1000, 37)], [(33, 500)], [(2, 30)]])
+    ref, _ = P.plant(base, P.params_of(base))
+    w = tile_batch(base, B)
+    if T > 1:  # the other query: the heads in another order
+        w.q = np.stack([w.q, np.roll(w.q, 1, axis=1)], axis=1)
+    ds = S.DeviceStep(w, k_cap=170)
+    ds.decode_step()
+    g = ds.results()
+    ds.run(fused=False)
+    n = ds.results()
+    assert_step_equals_calls(g, n, False, kept_in_merge(ds), f"{dtype} {B} x 2, {T} queries")
+    if T == 1:
+        for b in range(B):
+            check_sequence(f"{dtype} {B} x 2", w, n, b, ref[b % 3], b_src=b % 3)
