@@ -991,7 +991,6 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
     const float s_ls = P::TSTATS ? (a.tau_s_one ? s_lt : sum_over_quads(s.Ls_t)) : 0.f;
     combine_waves<DT, D, MODE, W>(a, s, *ws, lds_block, wave, part, g, b, M_v, ls_v, lm_v, s_lt, s_lm, s_ls);
   } else if constexpr (P::KEPT || P::TEXT) {
-    static_assert(!(P::VIS && P::TEXT), "both roles: several waves per work-group");
     const float s_lt = sum_over_quads(s.l_t);
     const float s_lm = P::TSTATS ? sum_over_quads(s.Lm_t) : 0.f;
     const float s_ls = P::TSTATS ? (a.tau_s_one ? s_lt : sum_over_quads(s.Ls_t)) : 0.f;
@@ -1018,7 +1017,7 @@ template <int DT, int D, int MODE>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(attend_waves(DT, MODE)))) void attend_kernel(
     const AttendArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[PassLds<DT, D, MODE, 1>::BYTES];
-  if (base_mode(MODE) == MODE_VIS && static_cast<int>(blockIdx.x) == a.nparts) {
+  if ((base_mode(MODE) & MODE_VIS) != 0 && static_cast<int>(blockIdx.x) == a.nparts) {
     if (blockIdx.y == 0) step_setup<D>(a, blockIdx.z);
     return;
   }
@@ -1111,7 +1110,7 @@ hipError_t launch_single(const AttendArgs& a, int mode, hipStream_t st, hipEvent
   const bool kept = base_mode(mode) == MODE_KEPT;
   int gx = a.nparts;
   if (kept) gx = a.nsplit;
-  else if (mode == MODE_VIS) gx = a.nparts + 1;  // the step setup
+  else if ((mode & MODE_VIS) != 0) gx = a.nparts + 1;  // the step setup
   else if (mode == MODE_TEXT_KEPT) gx = a.nparts + a.T * a.nsplit;
   const dim3 grid(gx, kept ? a.Hkv * a.T : a.Hkv, a.B);
   switch (mode) {
@@ -1123,6 +1122,13 @@ hipError_t launch_single(const AttendArgs& a, int mode, hipStream_t st, hipEvent
     case MODE_KEPT: return launch_one(attend_kernel<DT, D, MODE_KEPT | PG>, grid, 64, a, st, ev0, ev1);
     case MODE_KEPT | MODE_ZSPILL:
       return launch_one(attend_kernel<DT, D, MODE_KEPT | MODE_ZSPILL | PG>, grid, 64, a, st, ev0, ev1);
+    case MODE_BOTH:  // (both roles in one wave per part: fp32 only, see make_plan)
+      if constexpr (DT == VP_F32) return launch_one(attend_kernel<DT, D, MODE_BOTH | PG>, grid, 64, a, st, ev0, ev1);
+      return hipErrorInvalidValue;
+    case MODE_BOTH_STATS:
+      if constexpr (DT == VP_F32)
+        return launch_one(attend_kernel<DT, D, MODE_BOTH_STATS | PG>, grid, 64, a, st, ev0, ev1);
+      return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 }

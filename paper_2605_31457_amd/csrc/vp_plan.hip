@@ -102,6 +102,17 @@ Plan make_plan(const vp_shape& s) {
   // pairs, 56.0 and 50.9 at 288, 52.3 and 47.3 at 1024)
   p.text_waves = many_pairs ? 1 : p.waves;
   p.text_parts = many_pairs ? capped((VP_LATER_TEXT_WAVES + pairs - 1) / pairs, VP_MIN_TILES) : p.nparts;
+  // fp32 steps whose tiles give at most one wave per CU: one tile per single-wave part
+  // of both roles, so that no wave waits at the barrier of a part's merge (one head of 64:
+  // 384 tokens 23.8 -> 22.7 us per step, 1800 24.7 -> 23.6; 28/4 heads of 128: 600
+  // tokens 30.3 -> 29.7, 1.9k 31.0 -> 31.1; beyond, 304 tiles: 30.9 -> 34.0). fp32 only:
+  // the smallest bf16 steps gained from four waves (384 tokens 22.8 -> 22.3 us).
+  // A row capacity for kept rows beyond the cache's keeps four waves per part,
+  // whose workspace is smaller.
+  if (one_launch && s.dtype == VP_F32 && tiles <= 64 && pairs * tiles <= 256 && s.k_cap <= s.max_seq_len) {
+    p.waves = p.text_waves = 1;
+    p.nparts = p.text_parts = static_cast<int>(tiles);
+  }
   // Kept pass: the fewest kept rows per work-group (32, 64, 128, ...) that
   // keep the launch within one resident round (VP_KEPT_WGS work-groups), so no
   // work-group waits for a second round (the 64 x 32k batch: 128 rows, 1792
@@ -124,7 +135,7 @@ Plan make_plan(const vp_shape& s) {
   // layer of 4 x 3.3k tokens, 28/4 heads: 23.4 -> 17.5 us, 6 x 745, 32/8 heads: 19.6 -> 17.1; the steps
   // within 0.3 us). With two per CU the steps lose as much as the later layers
   // gain (2 x 3.6k tokens, 32/32 heads: 38.9 -> 40.5 and 23.6 -> 23.2 us).
-  if (one_launch && single_group && !many_pairs) {
+  if (p.waves > 1 && single_group && !many_pairs) {
     const int64_t kept = (static_cast<int64_t>(queries(s)) * p.nsplit + kPartWaves - 1) / kPartWaves;
     const int64_t room = round / pairs - kept;
     auto chain = [&](int64_t parts) { return (tiles + kPartWaves * parts - 1) / (kPartWaves * parts); };

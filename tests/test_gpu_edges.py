@@ -161,3 +161,24 @@ def test_later_layer_work_group_order(dtype, Hq, B, T):
     if T == 1:
         for b in range(B):
             check_sequence(f"{dtype} {B} x 2", w, n, b, ref[b % 3], b_src=b % 3)
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,B,L", [(4, 1, 64, 1, 33), (4, 1, 64, 1, 2048), (4, 1, 64, 1, 2049), (4, 1, 64, 16, 512),
+                                          (4, 1, 64, 17, 512), (28, 4, 128, 1, 2048), (28, 4, 128, 2, 1025),
+                                          (32, 8, 128, 2, 500)])
+@pytest.mark.parametrize("block_size", [0, 16, 32])
+def test_small_fp32_steps(Hq, Hkv, d, B, L, block_size):
+    """fp32 steps of one tile per single-wave part (up to 64 tiles, 256 over the
+    batch) and the four-wave parts next to them, contiguous and paged."""
+    base = small_workload(seed=79, B=2, Hq=Hq, Hkv=Hkv, d=d, lens=[L, max(1, L // 2 - 5)], dtype="f32",
+                          segs=[[(3, L // 2), (L // 2 + 7, L // 5)], [(0, L // 4)]])
+    ref, _ = P.plant(base, P.params_of(base))
+    w = tile_batch(base, B)
+    ds = S.DeviceStep(w, block_size=block_size, block_seed=4)
+    ds.decode_step()
+    g = ds.results()
+    for b in range(B):
+        check_sequence(f"{B} x {Hkv} x {L}", w, g, b, ref[b % 2], b_src=b % 2)
+    for fused in (True, False):
+        ds.run(fused=fused)
+        assert_step_equals_calls(g, ds.results(), fused, kept_in_merge(ds), f"{B} x {Hkv} x {L} fused={fused}")
