@@ -285,10 +285,10 @@ __device__ __forceinline__ void store_acc(float* dst, const f32x4 (&acc)[N], int
   }
 }
 
-// What a tile's logits are taken relative to: the running maximum, or zero while
-// no row but ones of logit -inf was seen (their weights are then 2^-inf = 0;
-// relative to the maximum of -inf they would be NaN)
-__device__ __forceinline__ float finite_or_zero(float m) { return m == kNegInf ? 0.f : m; }
+// A running maximum before any finite logit: the least float, not -inf, so that rows
+// of logit -inf weigh 2^-inf = 0 until then (relative to -inf they would be NaN).
+// Written out as -inf (an empty partial).
+constexpr float kNoLogit = -3.402823466e38f;
 
 enum TileClass : int { TILE_TEXT = 0, TILE_VIS = 1, TILE_MIXED = 2 };
 
@@ -558,11 +558,10 @@ struct Pass {
         Lm_v *= up ? fast_exp2((m_v - lmax) * a.inv_tau_m) : 1.f;
         m_v = up ? lmax : m_v;
       }
-      const float ref = finite_or_zero(m_v);
       float ts = 0.f, tm = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float d = FULL || (vis & (1u << i)) ? z[i] - ref : kNegInf;
+        const float d = FULL || (vis & (1u << i)) ? z[i] - m_v : kNegInf;
         ts += fast_exp2(d * a.inv_tau_s);
         tm += fast_exp2(d * a.inv_tau_m);
       }
@@ -615,12 +614,11 @@ struct Pass {
         }
         m_t = up ? tm : m_t;
       }
-      const float ref = finite_or_zero(m_t);
       float p[8];
       float ps = 0.f;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        p[i] = (att & (1u << i)) ? fast_exp2(z[i] - ref) : 0.f;
+        p[i] = (att & (1u << i)) ? fast_exp2(z[i] - m_t) : 0.f;
         ps += p[i];
       }
       l_t += ps;
@@ -628,7 +626,7 @@ struct Pass {
         float tm = 0.f, ts = 0.f;
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-          const float d = (att & (1u << i)) ? z[i] - ref : kNegInf;
+          const float d = (att & (1u << i)) ? z[i] - m_t : kNegInf;
           tm += fast_exp2(d * a.inv_tau_m);
           if (!a.tau_s_one) ts += fast_exp2(d * a.inv_tau_s);
         }
@@ -863,9 +861,9 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
   s.bstride = static_cast<size_t>(a.sb) * C::ESZ;
   s.bmask = paged ? (1 << a.bs_log2) - 1 : 0;
   if constexpr (!P::KEPT) s.init_row_step();
-  s.m_v = kNegInf;
+  s.m_v = kNoLogit;
   s.Ls_v = s.Lm_v = 0.f;
-  s.m_t = kNegInf;
+  s.m_t = kNoLogit;
   s.l_t = s.Lm_t = s.Ls_t = 0.f;
 #pragma unroll
   for (int i = 0; i < C::ACC_N; ++i) s.acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -974,16 +972,18 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
   if constexpr (P::VIS) {
     // merge the four lanes' statistics onto their common maximum
     M_v = max_over_quads(s.m_v);
-    const bool any = s.m_v != kNegInf;
+    const bool any = s.m_v != kNoLogit;
     const float fs = any ? fast_exp2((s.m_v - M_v) * a.inv_tau_s) : 0.f;
     const float fm = any ? fast_exp2((s.m_v - M_v) * a.inv_tau_m) : 0.f;
     ls_v = sum_over_quads(s.Ls_v * fs);
     lm_v = sum_over_quads(s.Lm_v * fm);
+    M_v = M_v == kNoLogit ? kNegInf : M_v;
     if (W == 1 && s.hv && s.a4 == 0) {
       float* st = a.stats + ((static_cast<size_t>(b) * a.T * a.Hq + s.h) * a.nparts + part) * 8;
       *reinterpret_cast<float4*>(st) = make_float4(M_v, ls_v, lm_v, 0.f);
     }
   }
+  s.m_t = s.m_t == kNoLogit ? kNegInf : s.m_t;
   if constexpr (W > 1) {
     if (setup) step_setup<D>(a, b);  // a wave without tiles
     const float s_lt = P::TEXT ? sum_over_quads(s.l_t) : 0.f;
