@@ -79,23 +79,28 @@ Plan make_plan(const vp_shape& s) {
   auto capped = [&](int64_t n, int64_t least) {
     return static_cast<int>(std::max<int64_t>(1, std::min(n, (tiles + least - 1) / least)));
   };
-  // A round is what is resident at a time. Rounded down: a second round costs more
-  // than the finer parts give (two rounds instead of one of fp32 rows of 128: 4 x 29k tokens 53.5
-  // -> 61.8 us per step, 48 pairs of 745 36.4 -> 42.0, 96 of 2k 61 -> 73; bf16 72 to 192 pairs
-  // 1.09 to 1.12 times), except where one part per pair leaves a good part of the round or of
-  // the second one idle: two parts there.
-  //   half a round to one (bf16): one and two parts 125.2 and 121.4 us at 264 pairs, 93.4 and 89.7 at
-  //   288, 104.4 and 103.0 at 504, but 105.8 and 109.0 at 384 (fp32 rows of 128: 98 and 108 at 160 pairs);
-  //   one round to one and a half: 113.4 and 107.9 at 640 pairs, 110.4 and 103.7 at 768
-  //   (fp32 rows of 128: 162.5 and 146.4 at 272 pairs, 191 and 179 at 384; beyond: 137 and 151 at 416)
+  // A round is what is resident at a time. Parts are rounded down to one: a second
+  // round of bf16 parts measured 1.09 to 1.12 times the step at 72 to 192 pairs. The exceptions:
+  // * fp32 rows of 128 (one work-group per CU) with more than 32 pairs and two tiles per
+  //   wave or more: two rounds. A batch's sequences differ in length, and with so few
+  //   work-groups the CUs of the short ones stay idle in one round (16 x 28/4 heads
+  //   x 3k to 10k tokens 103.6 and 94.3 us per step, 9 x 4k to 12k 85.1 and 75.1;
+  //   of equal length 98.3 and 101.6 at 16 x 7k, 60.5 and 64.4 at 96 pairs x 2k). Fewer
+  //   pairs or shorter sequences: one (4 x 11k 56.2 and 62.1, 48 pairs x 745 35.9 and 39.8).
+  // * two parts where one per pair leaves a good part of the round, or of the second
+  //   one, idle. bf16 above half a round, one and two parts: 125.2 and 121.4 us at
+  //   264 pairs, 93.4 and 89.7 at 288, 104.4 and 103.0 at 504, but 105.8 and 109.0 at 384.
+  //   Above one round: bf16 113.4 and 107.9 at 640, 110.4 and 103.7 at 768; fp32
+  //   rows of 128 162.5 and 146.4 at 272, 191 and 179 at 384, but 137 and 151 at 416.
   const int64_t round = resident_groups(s.dtype, s.head_dim);
   const bool single_group = round == 256;  // one work-group per CU
+  const bool two_rounds = single_group && pairs > 32 && pairs <= round && tiles >= 2 * kPartWaves * (2 * round / pairs);
   const bool two_parts =
       pairs > round ? 2 * pairs <= 3 * round
                     : !single_group && 2 * pairs > round && pairs < round && (4 * pairs < 3 * round || 8 * pairs >= 7 * round);
   const bool many_pairs = one_launch && pairs > 256;
   p.nparts = !one_launch ? capped((VP_TWO_LAUNCH_PARTS + pairs - 1) / pairs, min_tiles)
-                         : capped(two_parts ? 2 : round / pairs, min_tiles);
+                         : capped(two_parts ? 2 : (two_rounds ? 2 * round : round) / pairs, min_tiles);
   // A later layer's text pass has the context pass's parts, but with many pairs
   // single-wave parts, one to four per pair: they balance the text rows alone
   // better (a later layer with four-wave parts and here: 68.1 and 64.8 us at 264

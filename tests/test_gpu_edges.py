@@ -126,8 +126,10 @@ def _step_calls_and_own_text(tag, w, ref, n_ref):
 
 @pytest.mark.parametrize("dtype,Hkv,d,B,L", [
     # fp32 rows of 128 (one four-wave work-group per CU): parts of one round, fewer
-    # where the kept work-groups need slots, one per pair, two past a round, one again
-    ("f32", 2, 128, 2, 2900), ("f32", 4, 128, 4, 3300), ("f32", 8, 128, 6, 745), ("f32", 4, 128, 40, 290),
+    # where the kept work-groups need slots, of two rounds with more pairs, one per
+    # pair, two past a round, one again
+    ("f32", 2, 128, 2, 2900), ("f32", 4, 128, 4, 3300), ("f32", 8, 128, 6, 745), ("f32", 4, 128, 9, 3600),
+    ("f32", 4, 128, 40, 290), ("f32", 4, 128, 40, 800),
     ("f32", 4, 128, 64, 290), ("f32", 4, 128, 65, 290), ("f32", 4, 128, 96, 290), ("f32", 4, 128, 97, 290),
     # bf16: two parts above half a round, one from three quarters, two from seven
     # eighths, one at a round, two up to one and a half, one beyond
@@ -140,11 +142,11 @@ def test_parts_per_pair(dtype, Hkv, d, B, L):
     _step_calls_and_own_text(f"{dtype} {B} x {Hkv} x {L}", tile_batch(base, B), ref, 3)
 
 
-@pytest.mark.parametrize("dtype,Hq,B,T", [("bf16", 8, 1, 1), ("bf16", 8, 8, 1), ("bf16", 8, 9, 1), ("bf16", 14, 5, 2),
-                                          ("bf16", 14, 6, 2), ("f32", 4, 4, 1), ("f32", 4, 5, 1)])
+@pytest.mark.parametrize("dtype,Hq,B,T", [("bf16", 8, 1, 1), ("bf16", 8, 10, 1), ("bf16", 8, 11, 1), ("bf16", 14, 7, 2),
+                                          ("bf16", 14, 8, 2), ("f32", 4, 5, 1), ("f32", 4, 6, 1)])
 def test_later_layer_work_group_order(dtype, Hq, B, T):
     """Text and kept work-groups in one launch: interleaved while the kept ones (here
-    two per pair and query, rounded up) are at most a sixteenth of a round, all of the
+    two per pair and query, rounded up) are at most a twelfth of a round, all of the
     text ones first beyond."""
     base = small_workload(seed=78, B=3, Hq=Hq, Hkv=2, d=128, lens=[1300, 700, 40], dtype=dtype,
                           segs=[[(20, 900), (1000, 37)], [(33, 500)], [(2, 30)]])
