@@ -1063,14 +1063,15 @@ attend_text_kept_kernel(const AttendArgs a) {
   int x = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
   const unsigned pairs = gridDim.y * gridDim.z;
   const unsigned kept_groups = gridDim.x - a.nparts;  // of a pair
-  if (W > 1 && 16 * kept_groups * pairs > resident_groups(DT, D)) {
+  if (W > 1 && 12 * kept_groups * pairs > resident_groups(DT, D)) {
     // the text work-groups of every pair come first: they fill the launch's first
     // round by themselves, and the short kept ones follow as slots fall free. With
     // the two interleaved, the last pairs' text work-groups waited for that round
     // (a later layer at 72 (sequence, KV head) pairs x 10k tokens 53.5 -> 44.5 us,
     // 80 x 9k 52.7 -> 43.5, 256 x 4k 64.4 -> 55.5; kept ones first: 47.3, 44.9, 59.5).
     // With few kept work-groups that wait is short, and theirs at the end is not:
-    // interleaved (8 pairs x 8k tokens 14.4 us, text first 15.7; 16 x 9k 18.5 and 19.6)
+    // interleaved (a launch of 512 text and 16 kept ones, 8 pairs x 8k tokens, 14.4
+    // us, text first 15.7; 32 kept, 16 x 9k, 18.5 and 19.6; but 64 kept, 32 x 9k, 25.9 and 24.1)
     const unsigned n = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const unsigned n_text = a.nparts * pairs;
     const unsigned x0 = n < n_text ? 0 : a.nparts;
