@@ -192,8 +192,8 @@ vp_status vp_visual_mass(const vp_shape* shape, const vp_layout* layout, const v
  *   [1] when the text pass starts executing, [2] when it ends (both attached
  *       to that launch, hipExtLaunchKernel: [1]..[2] is its execution alone)
  *   [3] after the mass reduction    [4] after the scores kernel.
- * (With VP_PLAN_ONE_CONTEXT_LAUNCH and V given, [1]..[2] is the one launch of
- * both passes; see vp_step_plan.)
+ * (With VP_PLAN_ONE_CONTEXT_LAUNCH, [1]..[2] is the one launch of both passes,
+ * whether V is given or NULL, and [0] precedes it; see vp_step_plan.)
  * events may be NULL when n_events is 0. Results are identical to
  * vp_visual_mass. VP_ERR_RANGE if n_events is outside [0, VP_MASS_EVENTS].
  */
@@ -324,7 +324,7 @@ vp_status vp_decode_step_static(const vp_shape* shape, const vp_layout* layout, 
                                 void* out, void* stream);
 
 /*
- * vp_step_plan -- how vp_visual_mass (with V) and vp_decode_step will launch
+ * vp_step_plan -- how vp_visual_mass and vp_decode_step will launch
  * their kernels for this shape (pure host computation; for profiling and
  * benchmarks). flags is a bit set of
  *   VP_PLAN_ONE_CONTEXT_LAUNCH  the visual and text passes share one launch
@@ -340,13 +340,18 @@ vp_status vp_decode_step_static(const vp_shape* shape, const vp_layout* layout, 
  *                               pass); vp_sparse_decode_attn without that flag
  *                               keeps its kept pass, so its output then agrees
  *                               with theirs to rounding, not bit for bit.
- * (The same holds, without a flag, where batch * n_kv_heads exceeds 256 in
- * one context launch: a layer's own text pass has other
- * parts there.)
+ *   VP_PLAN_OWN_TEXT_PARTS      vp_sparse_decode_attn without VP_ATTN_TEXT_FROM_WORKSPACE
+ *                               splits the text rows differently from the step
+ *                               (one context launch, more than 256 (sequence, KV
+ *                               head) pairs): its output agrees with the
+ *                               step's to rounding, not bit for bit, and the
+ *                               text part that vp_visual_mass left in the workspace
+ *                               is gone after it.
  */
 #define VP_PLAN_ONE_CONTEXT_LAUNCH 1
 #define VP_PLAN_FUSED_TAIL 2
 #define VP_PLAN_KEPT_IN_MERGE 4
+#define VP_PLAN_OWN_TEXT_PARTS (1 << 3)
 vp_status vp_step_plan(const vp_shape* shape, const vp_params* params, int32_t* flags);
 
 /*

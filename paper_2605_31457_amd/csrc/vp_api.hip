@@ -561,7 +561,8 @@ vp_status vp_step_plan(const vp_shape* shape, const vp_params* params, int32_t* 
   if (!flags) return fail(VP_ERR_NULL, "flags is NULL");
   const Plan plan = make_plan(*shape);
   *flags = (use_dual(shape) ? VP_PLAN_ONE_CONTEXT_LAUNCH : 0) | (plan.sel_chunks == 1 ? VP_PLAN_FUSED_TAIL : 0) |
-           (plan.merge_kept ? VP_PLAN_KEPT_IN_MERGE : 0);
+           (plan.merge_kept ? VP_PLAN_KEPT_IN_MERGE : 0) |
+           (plan.text_parts != plan.nparts || plan.text_waves != plan.waves ? VP_PLAN_OWN_TEXT_PARTS : 0);
   return VP_OK;
 }
 

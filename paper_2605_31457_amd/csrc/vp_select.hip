@@ -9,16 +9,19 @@
 // Work-group c of row (b, u) reduces the per-part statistics of the row's heads
 // (every work-group of the row does, so none waits for another), scores the
 // visual ranks [c * chunk, (c + 1) * chunk) from the spilled logits and writes
-// them. With one chunk per row the same work-group selects (its keys in LDS,
-// or, beyond the LDS room, re-read from its own score stores); with several, each work-group publishes its scores (device-scope
+// them. With one chunk per row the same work-group selects; with several, each
+// work-group publishes its scores (device-scope
 // atomic stores, coherent across the XCDs) and, once they have completed,
 // counts itself in on the row's arrival counter (zeroed by the context pass of
 // the same step); the last to arrive reads every score of the row back with
-// device-scope loads and selects. No work-group ever waits for another.
+// device-scope loads and selects. No work-group ever waits for another. The selecting
+// work-group holds its keys in registers (max_vis up to 32768; a single chunk's pass through LDS
+// on the way, and where they would not fit there, from about 30 K, the row takes the
+// general path), else in LDS or, beyond its room, in its score stores.
 //
 // Latency: the statistics and the segment table (built by the context pass)
 // are requested at once at entry; the spilled logits of a thread's tokens (all heads) are one
-// batch of loads; the selection is the LDS radix select of vp_blocks.h.
+// batch of loads; the selection is the radix select of vp_blocks.h (counters in LDS).
 // Results equal those of the separate kernels (mass_finalize_kernel,
 // scores_kernel, budget rule, topk_kernel): the same device functions in the
 // same order.

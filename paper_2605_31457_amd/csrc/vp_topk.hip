@@ -3,8 +3,10 @@
 // One 1024-thread work-group (16 waves) per selection row (a sequence, or one
 // query or KV group of it; the row's sequence gives the visual tokens):
 //  1. wave 0 loads the sequence's segment table into LDS while the block maps
-//     the scores to order-preserving 32-bit keys, stages them in LDS (when
-//     they fit) and finds their min and max;
+//     the scores to order-preserving 32-bit keys and finds their min and max. Rows
+//     of up to 32768 tokens (max_vis) keep the keys in registers, 2 to 32 per
+//     thread; longer ones stage them in LDS where they fit (about 30.8 K keys
+//     beside the radix counters and the segment table) or read the scores again;
 //  2. radix select over the key range [min, max]: each pass histograms the
 //     surviving candidates on the next 13 bits of (key - lo) into 8192 LDS
 //     counters, a block-wide suffix scan finds the digit holding the k-th
@@ -15,11 +17,11 @@
 //     counter clears it while scanning. The result is the k-th largest key T
 //     and the number `need` of keys equal to T that are kept;
 //  3. ordered compaction: wave w owns a contiguous block of ranks (= position
-//     order). A first sweep counts its keys > T and == T with ballots; one
-//     block scan of those counts gives every wave its offsets; a second sweep
-//     keeps every key > T and the first `need` keys == T (ties go to the lower
-//     position) and writes positions in ascending order. No block barrier runs
-//     inside the sweeps.
+//     order) and keeps every key > T and the first `need` keys == T (ties go to
+//     the lower position), in ascending order. One block scan of the waves' counts
+//     gives every wave its offsets. Keys in registers: one ballot per slot, then
+//     every lane walks its own kept slots. Keys in LDS or memory: a first sweep counts
+//     with ballots, a second writes; no block barrier runs inside the sweeps.
 #include "vp_blocks.h"
 
 namespace vp {

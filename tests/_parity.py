@@ -30,6 +30,13 @@ def kept_in_merge(ds) -> bool:
     return bool(vp.vp_step_plan(ds.shape, ds.params) & vp.VP_PLAN_KEPT_IN_MERGE)
 
 
+def own_text_parts(ds) -> bool:
+    """A layer that reads its own text rows splits them differently from the step
+    (VP_PLAN_OWN_TEXT_PARTS): other orders of fp32 sums, so equal to rounding."""
+    from paper_2605_31457_amd import vp
+    return bool(vp.vp_step_plan(ds.shape, ds.params) & vp.VP_PLAN_OWN_TEXT_PARTS)
+
+
 def assert_step_equals_calls(step, calls, fused, kept_merged, ctx=""):
     """vp_decode_step against the four calls. With the text part taken from the
     workspace (fused) every output is the same bits (the same arithmetic, the

@@ -213,6 +213,18 @@ def test_header_plan_flags_match_binding():
         "VP_PLAN_KEPT_IN_MERGE": vp.VP_PLAN_KEPT_IN_MERGE}
 
 
+@pytest.mark.parametrize("B, dtype, want", [(64, vp.VP_BF16, 0), (65, vp.VP_BF16, 8), (64, vp.VP_F32, 0),
+                                            (65, vp.VP_F32, 8)])
+def test_step_plan_names_own_text_parts(L, B, dtype, want):
+    """More than 256 (sequence, KV head) pairs in one context launch: a layer's own
+    text rows are split differently from the step's (one bit past the flags above)."""
+    assert re.search(r"#define\s+VP_PLAN_OWN_TEXT_PARTS \(1 << 3\)", open(HEADER).read())
+    assert vp.VP_PLAN_OWN_TEXT_PARTS == 1 << 3
+    shape = _shape(batch=B, n_q_heads=16, head_dim=64, dtype=dtype, max_seq_len=600, max_vis=300,
+                   kv_stride_b=4 * 600 * 64, kv_stride_h=600 * 64, kv_stride_s=64)
+    assert vp.vp_step_plan(shape, _params()) & vp.VP_PLAN_OWN_TEXT_PARTS == want
+
+
 def _bench_shape(B, Hq, Hkv, S, n_vis, k_cap, **kw):
     return _shape(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, max_seq_len=S, max_vis=n_vis, max_segs=4, k_cap=k_cap,
                   kv_stride_b=Hkv * S * 128, kv_stride_h=S * 128, **kw)

@@ -10,7 +10,7 @@ import numpy as np
 import pytest
 import torch
 
-from _parity import assert_step_equals_calls, check_sequence, kept_in_merge, small_workload, tile_batch
+from _parity import assert_step_equals_calls, check_sequence, kept_in_merge, own_text_parts, small_workload, tile_batch
 from oracle import plant as P
 from oracle import vp_oracle as O
 from paper_2605_31457_amd import step as S
@@ -59,6 +59,8 @@ def test_many_sequence_and_kv_head_pairs(B, Hkv, d):
     ds, g = _check(f"{B} x {Hkv}", w, ref, 3)
     ds.run(fused=False)
     n = ds.results()
+    assert own_text_parts(ds) == (B * Hkv > 256)
+    assert_step_equals_calls(g, n, False, kept_in_merge(ds) or own_text_parts(ds), f"{B} x {Hkv} own text")
     for b in range(w.B):
         check_sequence(f"{B} x {Hkv} own text", w, n, b, ref[b % 3], b_src=b % 3)
 
@@ -76,6 +78,14 @@ def test_step_selection_with_one_work_group_per_row(n_vis):
     base = small_workload(seed=73, B=2, Hq=4, Hkv=1, d=64, lens=[n_vis + 60, 200], segs=[[(30, n_vis)], [(20, 150)]])
     ref, _ = P.plant(base, P.params_of(base))
     _check(f"256 rows of {n_vis}", tile_batch(base, 256), ref, 2, max_vis=n_vis)
+
+
+def test_step_selection_with_one_work_group_per_row_past_the_lds():
+    """256 rows with room for 32000 keys each, more than a work-group's LDS but not than
+    its registers hold: the row's keys take the general path, in LDS where they fit."""
+    base = small_workload(seed=80, B=2, Hq=4, Hkv=1, d=64, lens=[3000, 200], segs=[[(30, 2900)], [(20, 150)]])
+    ref, _ = P.plant(base, P.params_of(base))
+    _check("256 rows of 32000", tile_batch(base, 256), ref, 2, max_vis=32000)
 
 
 @pytest.mark.parametrize("n", [1, 63, 2047, 2048, 2049, 4096, 4097, 8193, 16384, 16385, 32768, 32769])
@@ -118,8 +128,8 @@ def _step_calls_and_own_text(tag, w, ref, n_ref):
     ds, g = _check(tag, w, ref, n_ref)
     ds.run(fused=False)
     n = ds.results()
-    own_parts = w.B * w.Hkv > 256
-    assert_step_equals_calls(g, n, False, kept_in_merge(ds) or own_parts, tag)
+    assert own_text_parts(ds) == (w.B * w.Hkv > 256)
+    assert_step_equals_calls(g, n, False, kept_in_merge(ds) or own_text_parts(ds), tag)
     for b in range(w.B):
         check_sequence(f"{tag}, own text", w, n, b, ref[b % n_ref], b_src=b % n_ref)
 
