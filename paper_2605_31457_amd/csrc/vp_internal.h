@@ -47,7 +47,7 @@ constexpr int resident_groups(int dtype, int head_dim) { return 256 * (dtype == 
 struct Plan {
   int nparts;   // context-pass work-groups per (sequence, KV head); part p takes
                 // the 32-row tiles p, p + nparts, p + 2 nparts, ...
-  int waves;    // waves per context-pass work-group (kPartWaves, or 1 with the passes in two launches)
+  int waves;    // waves per context-pass work-group (kPartWaves; 1: the passes in two launches, small fp32 steps)
   int split;    // kept rows per kept-pass work-group (multiple of 32)
   int nsplit;   // ceil(k_cap / split)
   int text_parts;  // parts and waves of the text pass that a later layer runs for itself

@@ -16,8 +16,8 @@ int queries(const vp_shape& s) { return s.n_queries > 1 ? s.n_queries : 1; }
 int rows_per_query(const vp_shape& s) { return s.scope == VP_SCOPE_KV_GROUP ? s.n_kv_heads : 1; }
 int rows_per_seq(const vp_shape& s) { return queries(s) * rows_per_query(s); }
 
-// Waves of the one launch of both passes: one resident round (8 waves per CU x
-// 256 CUs), so no work-group waits for a second round, shared by kPartWaves
+// Parts of the one launch of both passes: one resident round of work-groups
+// (resident_groups), so that none waits for a second one, shared by kPartWaves
 // waves per part: a part's statistics and value partial are written once for
 // four waves, where one wave per part and role left the select and merge
 // launches 256 partials per head to read at one 30k-token sequence (per pass
@@ -43,8 +43,11 @@ int rows_per_seq(const vp_shape& s) { return queries(s) * rows_per_query(s); }
 // Both context passes in one launch: saves a launch and overlaps the two
 // passes' latency chains where the cache is small; kept apart otherwise, so
 // the visual pass's logit writes stay out of the text pass's read stream.
-// Measured with one wave per part: the 8 x 10.5k batch of the 72B shape (22k
-// tiles) gained 6 us from the one launch; the 64 x 32k batch (262k tiles) lost 100 us.
+// Two launches and one, us per step with four-wave parts: 8 x 9.1k tokens, 28/4 heads (9k
+// tiles) 51.3 and 46.2, 16 ragged (25k) 70.3 and 68.8, 16 x 12k (24k) 85.7 and
+// 85.5; past the line neither wins: 127.4 and 126.1 at 40k tiles, 132.0 and 126.9 at
+// 52k (ragged), but 108.2 and 111.3 at 33k, 132.1 and 135.7 at 44k, 174.2 and 179.4 at
+// 59k; the 64 x 32k batch (262k tiles) lost 100 us (one-wave parts).
 #ifndef VP_DUAL_MAX_TILES
 #define VP_DUAL_MAX_TILES 32768  // 32-row tiles over the batch and KV heads
 #endif
@@ -67,7 +70,7 @@ bool use_dual(const vp_shape* s) {
 
 Plan make_plan(const vp_shape& s) {
   Plan p{};
-  // Context pass: parts of kPartWaves waves (one launch) or one wave (two
+  // Context pass: parts of kPartWaves waves (one launch; small fp32 steps one wave) or one wave (two
   // launches). Tiles are dealt out cyclically, so every part sees the sequence's own mix of visual and text rows: consecutive
   // work-groups land on different XCDs, and contiguous chunks would hand whole
   // XCDs only visual (K) or only text (K + V) rows.
