@@ -342,8 +342,9 @@ vp_status vp_decode_step_static(const vp_shape* shape, const vp_layout* layout, 
  *                               with theirs to rounding, not bit for bit.
  *   VP_PLAN_OWN_TEXT_PARTS      vp_sparse_decode_attn without VP_ATTN_TEXT_FROM_WORKSPACE
  *                               splits the text rows differently from the step
- *                               (one context launch, more than 256 (sequence, KV
- *                               head) pairs): its output agrees with the
+ *                               (one context launch, and more than 256 (sequence,
+ *                               KV head) pairs or few text rows beside the kept
+ *                               ones): its output agrees with the
  *                               step's to rounding, not bit for bit, and the
  *                               text part that vp_visual_mass left in the workspace
  *                               is gone after it.

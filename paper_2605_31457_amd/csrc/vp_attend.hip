@@ -1071,7 +1071,8 @@ attend_text_kept_kernel(const AttendArgs a) {
     // 80 x 9k 52.7 -> 43.5, 256 x 4k 64.4 -> 55.5; kept ones first: 47.3, 44.9, 59.5).
     // With few kept work-groups that wait is short, and theirs at the end is not:
     // interleaved (a launch of 512 text and 16 kept ones, 8 pairs x 8k tokens, 14.4
-    // us, text first 15.7; 32 kept, 16 x 9k, 18.5 and 19.6; but 64 kept, 32 x 9k, 25.9 and 24.1)
+    // us, text first 15.7; 32 kept, 16 x 9k, 18.5 and 19.6; but 64 kept, 32 x 9k, 25.9
+    // and 24.1)
     const unsigned n = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const unsigned n_text = a.nparts * pairs;
     const unsigned x0 = n < n_text ? 0 : a.nparts;

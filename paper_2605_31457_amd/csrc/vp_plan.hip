@@ -150,6 +150,23 @@ Plan make_plan(const vp_shape& s) {
     if (p.nparts > room && 4 * room >= 3 * p.nparts && chain(room) == chain(p.nparts))
       p.nparts = p.text_parts = static_cast<int>(room);
   }
+  // Single-wave parts also for a later layer's few text rows: where the four-wave
+  // parts and the kept work-groups exceed a round and a wave has at most two tiles of
+  // text (as the row capacities have it), the second round of short work-groups costs
+  // more than the walk over the text; single-wave parts and the kept splits
+  // share one round (a later layer of 16 x 300 text and 4000 visual tokens, 28/4 heads: 17.0
+  // -> 14.1 us, 60 x 250 and 1000 21.2 -> 18.9, fp32 16 x 300 and 4000 35.7 -> 24.7; at
+  // 2.4 to 2.8 tiles the four-wave parts are as fast).
+  const int64_t kept_splits = static_cast<int64_t>(queries(s)) * p.nsplit;
+  const int64_t text_tiles = s.max_seq_len > s.max_vis ? (s.max_seq_len - s.max_vis + 31) / 32 : 0;
+  const int single_parts = capped((VP_LATER_TEXT_WAVES + pairs - 1) / pairs, VP_MIN_TILES);
+  const bool few_text = p.waves > 1 && pairs > 16 && !many_pairs &&
+                        pairs * (p.nparts + (kept_splits + kPartWaves - 1) / kPartWaves) > round &&
+                        text_tiles <= 2 * kPartWaves * p.nparts && (single_parts + kept_splits) * pairs <= VP_KEPT_WGS;
+  if (few_text) {
+    p.text_waves = 1;
+    p.text_parts = single_parts;
+  }
   // A later layer (its own text rows, the anchor's kept list) launches its text
   // and kept passes together: with four-wave text parts, which fill a round by
   // themselves, when the kept splits are at most half a round of waves (text waves not
@@ -158,8 +175,7 @@ Plan make_plan(const vp_shape& s) {
   // 1-sequence batch, 381.9 -> 351.9 at the 72B-class loop); beyond one round
   // the text pass is split over two (the 64 x 32k batch: 3081 -> 3663 us).
   p.text_kept_one_launch =
-      p.text_waves > 1 ? pairs * queries(s) * p.nsplit <= VP_KEPT_WGS / 2
-                       : (p.text_parts + static_cast<int64_t>(queries(s)) * p.nsplit) * pairs <= VP_KEPT_WGS;
+      p.text_waves > 1 ? pairs * kept_splits <= VP_KEPT_WGS / 2 : (p.text_parts + kept_splits) * pairs <= VP_KEPT_WGS;
   // A step whose kept pass would be a handful of work-groups folds the kept
   // rows into the merge (their K and V rows read there): bf16 caches, every
   // text part and kept row in one batch per head.
@@ -170,24 +186,36 @@ Plan make_plan(const vp_shape& s) {
   const size_t B = s.batch, Hq = static_cast<size_t>(s.n_q_heads) * queries(s), d = s.head_dim;
   p.zs_rows = ((s.max_seq_len + 31) / 32) * 32;
   p.zs_gp = queries(s) * (s.n_q_heads / s.n_kv_heads) <= 8 ? 8 : 16;
-  size_t off = 0;
-  p.zs = off;
-  off = align256(off + B * static_cast<size_t>(s.n_kv_heads) * p.zs_rows * static_cast<size_t>(p.zs_gp) * 4);
-  p.stats = off;
-  const size_t part_slots = std::max(p.nparts, p.text_parts);
-  off = align256(off + B * Hq * part_slots * 8 * 4);
-  p.acc = off;
-  off = align256(off + B * Hq * part_slots * d * 4);
-  p.head = off;
-  off = align256(off + B * Hq * 2 * 4);
-  p.kstats = off;
-  off = align256(off + B * Hq * p.nsplit * 2 * 4);
-  p.kacc = off;
-  off = align256(off + B * Hq * p.nsplit * d * 4);
   const size_t rows = B * static_cast<size_t>(rows_per_seq(s));
-  p.segtab = off;
-  off = align256(off + B * kSegTableBytes);
-  p.total = off;
+  auto carve = [&] {
+    size_t off = 0;
+    p.zs = off;
+    off = align256(off + B * static_cast<size_t>(s.n_kv_heads) * p.zs_rows * static_cast<size_t>(p.zs_gp) * 4);
+    p.stats = off;
+    const size_t part_slots = std::max(p.nparts, p.text_parts);
+    off = align256(off + B * Hq * part_slots * 8 * 4);
+    p.acc = off;
+    off = align256(off + B * Hq * part_slots * d * 4);
+    p.head = off;
+    off = align256(off + B * Hq * 2 * 4);
+    p.kstats = off;
+    off = align256(off + B * Hq * p.nsplit * 2 * 4);
+    p.kacc = off;
+    off = align256(off + B * Hq * p.nsplit * d * 4);
+    p.segtab = off;
+    off = align256(off + B * kSegTableBytes);
+    p.total = off;
+  };
+  carve();
+  if (few_text && p.total > VP_STATIC_SCRATCH_BYTES) {
+    // not where only the single-wave parts' partials take the step past the static scratch
+    const Plan own = p;
+    p.text_waves = p.waves;
+    p.text_parts = p.nparts;
+    p.text_kept_one_launch = pairs * kept_splits <= VP_KEPT_WGS / 2;
+    carve();
+    if (p.total > VP_STATIC_SCRATCH_BYTES) p = own;
+  }
   // Select kernel: chunks of whole rounds (a round scores 1024 / lanes-per-token
   // visual ranks), enough rounds per chunk that the launch has about
   // VP_SELECT_WGS work-groups, so the spilled logits stream through many CUs.

@@ -213,14 +213,17 @@ def test_header_plan_flags_match_binding():
         "VP_PLAN_KEPT_IN_MERGE": vp.VP_PLAN_KEPT_IN_MERGE}
 
 
-@pytest.mark.parametrize("B, dtype, want", [(64, vp.VP_BF16, 0), (65, vp.VP_BF16, 8), (64, vp.VP_F32, 0),
-                                            (65, vp.VP_F32, 8)])
-def test_step_plan_names_own_text_parts(L, B, dtype, want):
-    """More than 256 (sequence, KV head) pairs in one context launch: a layer's own
-    text rows are split differently from the step's (one bit past the flags above)."""
+@pytest.mark.parametrize("B, n_vis, dtype, want", [
+    (64, 64, vp.VP_BF16, 0), (65, 64, vp.VP_BF16, 8), (64, 64, vp.VP_F32, 0), (65, 64, vp.VP_F32, 8),
+    # few text rows: at most two tiles per wave of the step's parts
+    (64, 88, vp.VP_BF16, 8), (64, 87, vp.VP_BF16, 0), (8, 590, vp.VP_BF16, 0)])
+def test_step_plan_names_own_text_parts(L, B, n_vis, dtype, want):
+    """More than 256 (sequence, KV head) pairs in one context launch, or few text
+    rows beside the kept ones of a full round: a layer's own text rows are split
+    differently from the step's (one bit past the flags above)."""
     assert re.search(r"#define\s+VP_PLAN_OWN_TEXT_PARTS \(1 << 3\)", open(HEADER).read())
     assert vp.VP_PLAN_OWN_TEXT_PARTS == 1 << 3
-    shape = _shape(batch=B, n_q_heads=16, head_dim=64, dtype=dtype, max_seq_len=600, max_vis=300,
+    shape = _shape(batch=B, n_q_heads=16, head_dim=64, dtype=dtype, max_seq_len=600, max_vis=n_vis,
                    kv_stride_b=4 * 600 * 64, kv_stride_h=600 * 64, kv_stride_s=64)
     assert vp.vp_step_plan(shape, _params()) & vp.VP_PLAN_OWN_TEXT_PARTS == want
 
