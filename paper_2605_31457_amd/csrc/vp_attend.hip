@@ -382,7 +382,7 @@ struct Pass {
         n.w.seek(t0);
         n.cls = classify(n.w, t0, min(t0 + 32, r1));
         if constexpr (PAGED) {
-          if (lane < 32) n.blk = block_of(min(t0 + lane, L - 1));
+          if (active(n) && lane < 32) n.blk = block_of(min(t0 + lane, L - 1));
         }
       }
     }
@@ -946,9 +946,9 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
       step_setup<D>(a, b);
       setup = false;
     }
+    if (!act) continue;  // (nothing was copied: no wait)
     // the copies have landed in LDS once the vector-memory counter drains
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    if (!act) continue;
     unsigned char* kblk = lds;
     unsigned char* vblk = lds + C::SUB_ROWS_BYTES;
     float* stage = reinterpret_cast<float*>(vblk + VB);
