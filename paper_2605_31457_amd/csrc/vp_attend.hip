@@ -791,7 +791,8 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
   using P = Pass<DT, D, MODE>;
   using Q = PassLds<DT, D, MODE, W>;
   constexpr int VB = Q::VB;
-  constexpr bool PAIRS = P::VIS && P::ATTN;  // two visual tiles per step
+  constexpr bool BOTH = P::VIS && P::ATTN;  // both roles
+  constexpr bool PAIRS = BOTH && W > 1;     // two visual tiles per step (single-wave parts of both roles have one tile)
   unsigned char* lds = lds_block + wave * Q::BYTES;
   lds_byte* lds_dma = (lds_byte*)lds;  // the copies' view of it (converted once: a generic pointer may be null)
 
@@ -874,7 +875,7 @@ __device__ __forceinline__ void attend_body(const AttendArgs& a, unsigned char* 
   // a wave of both roles needs its first tile's K rows whatever they are: they are
   // requested before the segments are known
   bool k_early = false;
-  if constexpr (PAIRS && !P::PAGED) {
+  if constexpr (BOTH && !P::PAGED) {
     k_early = s.even && s.r0 + 32 <= s.L;
     if (k_early) s.copy_even_rows(s.Kb + static_cast<size_t>(s.r0) * s.rstride, lds_dma);
   }
