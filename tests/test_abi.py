@@ -228,6 +228,16 @@ def test_step_plan_names_own_text_parts(L, B, n_vis, dtype, want):
     assert vp.vp_step_plan(shape, _params()) & vp.VP_PLAN_OWN_TEXT_PARTS == want
 
 
+@pytest.mark.parametrize("S, want", [(12288, 8), (12700, 0)])
+def test_own_text_parts_stay_inside_the_static_scratch(L, S, want):
+    """A shape whose step fits the library's static scratch fits it still: where only
+    a later layer's single-wave text parts would not, it keeps the step's parts."""
+    shape = _shape(batch=16, max_seq_len=S, max_vis=11000, k_cap=512, kv_stride_b=4 * S * 128, kv_stride_h=S * 128)
+    scratch = int(re.search(r"VP_STATIC_SCRATCH_BYTES \((\d+)u << 20\)", open(HEADER).read())[1]) << 20
+    assert vp.vp_workspace_size(shape) <= scratch
+    assert vp.vp_step_plan(shape, _params()) & vp.VP_PLAN_OWN_TEXT_PARTS == want
+
+
 def _bench_shape(B, Hq, Hkv, S, n_vis, k_cap, **kw):
     return _shape(batch=B, n_q_heads=Hq, n_kv_heads=Hkv, max_seq_len=S, max_vis=n_vis, max_segs=4, k_cap=k_cap,
                   kv_stride_b=Hkv * S * 128, kv_stride_h=S * 128, **kw)
