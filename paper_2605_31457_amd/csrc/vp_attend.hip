@@ -381,18 +381,23 @@ struct Pass {
       if (t0 < r1) {
         n.w.seek(t0);
         n.cls = classify(n.w, t0, min(t0 + 32, r1));
-        if constexpr (PAGED) {
+        if constexpr (PAGED && !(VIS && TEXT)) {
           if (active(n) && lane < 32) n.blk = block_of(min(t0 + lane, L - 1));
         }
+      }
+      // a wave of both roles needs the ids of every tile: no branch around the load
+      // (blocks of 16 rows, 64 pairs x 9.1k tokens: 73.7 us per step with one, 72.0
+      // without). Tiles past the end and empty sequences read an entry of the
+      // sequence's own row, which is not used
+      if constexpr (PAGED && VIS && TEXT) {
+        if (lane < 32) n.blk = block_of(max(min(t0 + lane, L - 1), 0));
       }
     }
     return n;
   }
 
-  // paged caches: the physical block of position p (of each of a tile's rows: the
-  // position that row_pos will read, clipped ones included). Only called where the
-  // tile has rows, so 0 <= p < L: waves without tiles, and every wave of an empty
-  // sequence, read no entry of the block table
+  // paged caches: the physical block of position p >= 0 (of each of a tile's rows: the
+  // position that row_pos will read, clipped ones included)
   __device__ __forceinline__ int block_of(int p) const {
     return bt[p >> __builtin_ctz(static_cast<unsigned>(bmask + 1))];
   }
